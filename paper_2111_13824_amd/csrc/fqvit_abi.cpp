@@ -64,6 +64,15 @@ fq_status lis_constants(float s_logit, int32_t bits, int32_t n, int32_t Lk,
     k->fp_ok = qlmax < (1ull << 24) &&
                (unsigned __int128)(2 * (uint64_t)Lk + 1) * ((unsigned __int128)qlmax << n) <
                    ((unsigned __int128)1 << 52);
+    // The screened float path divides by d through a signed 24-bit
+    // multiply-high: floor(a / d) for a in [-n d, d) scaled by 2^s_pre.  With
+    // ds = d << s_pre in (512, 1024] (or d itself when larger; fp_ok keeps it
+    // below 2^11) and n <= 30, n ds < 2^23 and n ds^2 < 2^32, so it is exact.
+    k->s_pre = 0;
+    while ((d << k->s_pre) <= 512) ++k->s_pre;
+    k->s_magic = (int32_t)((1ull << 32) / (d << k->s_pre));
+    k->s_add = (float)((double)qb - (double)d + 1.0 - 8388608.0);
+    k->s_qc = (float)qc;
     return FQ_OK;
 }
 

@@ -59,6 +59,11 @@ struct LisConsts {
     // values exactly in binary64) is valid when q_b^2 + q_c < 2^24 and
     // (2 Lk + 1)(q_b^2 + q_c) 2^n < 2^52.
     int32_t fp_ok;
+    // Constants of the screened float path's I-Exp (set when fp_ok).
+    int32_t s_pre;      // pre-shift making (d_ln2 << s_pre) > 512
+    int32_t s_magic;    // floor(2^32 / (d_ln2 << s_pre)) < 2^23
+    float s_add;        // q_b - d_ln2 + 1 - 2^23
+    float s_qc;         // q_c
 };
 
 struct LisArgs {

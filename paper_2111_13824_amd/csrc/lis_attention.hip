@@ -357,6 +357,8 @@ hipError_t launch_lis(const LisArgs& a, hipStream_t stream) {
     p.out_vec = fused && (a.d % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.out) & 15) == 0);
     // LDS of the row-wise output stores: one 16 x (dpad + 4) int32 block per wavefront
     const size_t out_lds = p.out_vec ? (size_t)4 * 16 * (p.dpad + 4) * sizeof(int32_t) : 0;
+    // the unit kernel's region per wavefront, which an undecided chunk also uses
+    const size_t unit_lds = fused ? (size_t)unit_lds_dwords(dt) * sizeof(int32_t) : 0;
     p.n_logits = a.G * (int64_t)a.Lq * a.Lk;
     p.n_bias = a.bias ? (int64_t)a.Hb * a.Lq * a.Lk : 0;
     p.tab_bytes = 0;
@@ -376,7 +378,7 @@ hipError_t launch_lis(const LisArgs& a, hipStream_t stream) {
         u.ld = u.kb + 8;
         u.vt_bytes = fused ? u.dpad * u.ld * (int)sizeof(uint16_t) : 0;
         const int wpu = unit_waves(nc, tiles16);
-        size_t lds = (size_t)u.vt_bytes + out_lds / 4 * wpu;
+        size_t lds = (size_t)u.vt_bytes + unit_lds * wpu;
         // codes only, dense rows: each wavefront gathers its tile's code rows
         // in LDS and writes them as one span
         const int row_bytes = a.k.top > 15 ? a.Lk : (a.Lk + 1) / 2;

@@ -133,9 +133,9 @@ __device__ __forceinline__ double row4_sum(double v) {
 // threads take consecutive key quads, so a wavefront's stores to one column
 // row are contiguous.  Conversion: the byte b of v is flipped to b ^ 0x80
 // (= v + 128, unsigned), converted to float and reduced by 128 + zp, which is
-// exact; the bf16 pattern is the high half of that float.  Keys past Lk and
-// columns past d hold -zp: those keys get P = 0 and those columns are never
-// stored, so any finite value is harmless.
+// exact; the bf16 pattern is the high half of that float.  Keys past Lk are
+// loaded as zp and so hold 0 (the float path's P of a masked key is not 0);
+// columns past d hold any finite value and are never stored.
 // ---------------------------------------------------------------------------
 constexpr int kStageItems = 2;     // items per thread and stage: kcnt dpad / 64 <= 512
 
@@ -154,9 +154,10 @@ __device__ __forceinline__ u32x4 load_v16(const int8_t* vrow, int dd, int d, boo
 
 template <int NTHREADS = kBlock>
 __device__ __forceinline__ void stage_load(StageRegs& sr, const int8_t* vg, int Lk, int d,
-                                           int ncg, int k0, int kcnt, bool vec_ok) {
+                                           int ncg, int k0, int kcnt, int zp, bool vec_ok) {
     const int nquads = kcnt >> 2;
     const int nitems = nquads * ncg;
+    const uint32_t pad = (uint32_t)(zp & 0xFF) * 0x01010101u;
 #pragma unroll
     for (int it = 0; it < kStageItems; ++it) {
         const int idx = (int)threadIdx.x + it * NTHREADS;
@@ -167,7 +168,7 @@ __device__ __forceinline__ void stage_load(StageRegs& sr, const int8_t* vg, int 
 #pragma unroll
         for (int t = 0; t < 4; ++t)
             sr.w[it][t] = (ok && j + t < Lk) ? load_v16(vg + (int64_t)(j + t) * d, dd, d, vec_ok)
-                                             : u32x4{0u, 0u, 0u, 0u};
+                                             : u32x4{pad, pad, pad, pad};
     }
 }
 
@@ -208,7 +209,7 @@ __device__ __forceinline__ void stage_store(const StageRegs& sr, uint16_t* vt, i
 __device__ __forceinline__ void stage_vt(uint16_t* vt, int ld, const int8_t* vg, int Lk, int d,
                                          int ncg, int k0, int kcnt, int zp, bool vec_ok) {
     StageRegs sr;
-    stage_load(sr, vg, Lk, d, ncg, k0, kcnt, vec_ok);
+    stage_load(sr, vg, Lk, d, ncg, k0, kcnt, zp, vec_ok);
     stage_store(sr, vt, ld, ncg, kcnt, zp);
 }
 
@@ -511,6 +512,103 @@ __device__ __forceinline__ float third_floor_f32(double S2) {
     return (double)f > q ? __int_as_float(__float_as_int(f) - 1) : f;
 }
 
+// ---------------------------------------------------------------------------
+// Screened float path.  The codes are first taken from binary32 values, and a
+// 32-key chunk with a decision that rounding could have changed (about one
+// chunk in a thousand) takes its codes again from the binary64 values above.
+// Per key this costs 17 vector instructions where the binary64 form takes 27.
+// The kernels are bound by vector issue: attention from Q and K on ViT-B/16
+// (768 x 197 x 197) 36.6 -> 30.0 us, the fused head there 42.0 -> 40.3 us (its
+// loads bound it then) and on Swin-S (6144 x 49 x 49) 32.1 -> 29.4 us.
+//
+//   * I-Exp: e' = qL 2^-z (the value scaled by 2^-n, which no code depends on)
+//     as a binary32 pattern.  Exact (screen_iexp).
+//   * Row sum: the 8 keys of a lane's chunk in a binary32 tree of depth 3, the
+//     chunks and lanes in binary64: S' = S (1 + a), |a| < 3.01 2^-24.
+//   * Code: with X = 4 S / 3, m = floor(log2((X + 2 e / 3) / e)).  With
+//     T = screen_top + 1 and Y = fl(e c + Xs), Xs = X' 2^-T (1 + 6 2^-24) rounded
+//     to binary32 and c = 2/3 2^-T rounded up, Y exceeds (X + 2 e / 3) 2^-T by a
+//     relative error in (0, 12 2^-24] (a, the roundings of Xs and of the fma
+//     stay below 5.01 2^-24 together; the bias adds 6 2^-24, and c at most
+//     2^-23 / 3).  The difference B of the patterns of e and Y is 2^23 times the
+//     piecewise linear logarithm of their quotient, so its computed value lies
+//     in [B - 12, B): floor(B / 2^23) can be wrong only when the computed
+//     value's residue modulo 2^23 is at least 2^23 - 12.  Otherwise it is
+//     T - 1 - m (an exact power of two, where the quotient of the true B would
+//     count one too many, computes just below it and is caught).  The
+//     subtraction saturates at 0: min(m, top).
+//   * [2S < 3e]: only the row maximum (u = 0) can satisfy it, when e0 > X / 2.
+//     Y is then Xs, whose quotient by e0 lies in [4/3, 2) 2^-T: one code less.
+//     The comparison errs only towards the larger code, and a row whose X / 2
+//     is within 2^-18 of e0 counts as undecided.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kScreenZone = 16;      // residues of the last 16 of 2^23 are undecided
+
+struct ScreenRow {
+    float Xs;       // 4 S / 3 2^-T, biased up
+    float tau;      // 2 S / 3 (scaled by 2^-n), biased up by more than its error
+    float c;        // 2 / 3 2^-T, rounded up (uniform)
+    uint64_t tie;   // lanes whose row has X / 2 too close to e0 to tell (uniform)
+};
+
+// T - 1, where T is the power the quotient is scaled by: top, but at most 62
+// (no code exceeds n + 12 <= 42, so wider codes are never cut at top).
+__device__ __forceinline__ int screen_top(const LisConsts& k) { return min(k.top, 62); }
+
+// e 2^-n of one key as binary32 bits.  With u = max - v clamped at n d (d =
+// |q_ln2|) and a = d - 1 - u, -z = floor(a / d) and s = a + z d in [0, d), so
+// q_p + q_b = s + (q_b - d + 1).  a is carried with the pattern of 2^23 added:
+// the 24-bit operations see a itself, and a + z d is the pattern of the float
+// 2^23 + s, which needs no conversion.  c = max - (d - 1) - 0x4B000000 is the
+// row's, so v - c is a plus the pattern (|v| < 2^30: no wrap; a masked key's
+// INT_MIN is clamped like any other).  Every value is an integer below 2^24.
+constexpr int32_t kFloat23 = 0x4B000000;
+
+__device__ __forceinline__ int32_t screen_c(int mx, const LisConsts& k) {
+    return (int32_t)((uint32_t)mx - (k.d_ln2 - 1u) - (uint32_t)kFloat23);
+}
+
+// P0: the pre-shift is known to be 0 (d > 512).
+template <bool P0 = false>
+__device__ __forceinline__ uint32_t screen_iexp(int v, int32_t c, const LisConsts& k) {
+    const int32_t lo = kFloat23 - (int32_t)(k.u_max - k.d_ln2 + 1u);
+    const int32_t a = max((int32_t)((uint32_t)v - (uint32_t)c), lo);
+    const int32_t as = P0 ? a : (int32_t)((uint32_t)a << k.s_pre);
+    // written out: the compiler would take a 64-bit multiply-add for the second
+    int32_t nz, f;      // nz = -z
+    asm("v_mul_hi_i32_i24 %0, %1, %2" : "=v"(nz) : "s"(k.s_magic), "v"(as));
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(f) : "v"(nz), "s"(-(int32_t)k.d_ln2), "v"(a));
+    const float w = __int_as_float(f) + k.s_add;
+    const float qL = __builtin_fmaf(w, w, k.s_qc);
+    // bits(qL) - z 2^23: z <= 30 and qL >= 1, so the result stays normal
+    return ((uint32_t)nz << 23) + __float_as_uint(qL);
+}
+
+__device__ __forceinline__ ScreenRow screen_row(double S, const LisConsts& k) {
+    const int T = screen_top(k) + 1;
+    ScreenRow st;
+    st.Xs = (float)(S * ldexp(4.0 / 3.0 * (1.0 + 6.0 * 0x1p-24), -T));
+    st.tau = (float)(S * (2.0 / 3.0 * (1.0 + 0x1p-19)));
+    st.c = __int_as_float(0x3F2AAAAB - (T << 23));       // 2/3 rounded up, scaled
+    const float e0 = (float)(k.qb * k.qb + k.qc);
+    st.tie = __ballot(fabsf(st.tau - e0) < e0 * 0x1p-18f);
+    return st;
+}
+
+// B of one key from its e bits: (top - code) 2^23 + residue, saturated at 0.
+__device__ __forceinline__ uint32_t screen_key(uint32_t eb, const ScreenRow& st) {
+    const float e = __uint_as_float(eb);
+    const float y = __builtin_fmaf(e, st.c, st.Xs);
+    const float ys = e > st.tau ? st.Xs : y;
+    return __builtin_elementwise_sub_sat(eb, __float_as_uint(ys));
+}
+
+// An undecided key somewhere in the wavefront: chk is the largest residue
+// (shifted to the top 23 bits) over the lane's keys.
+__device__ __forceinline__ bool screen_failed(uint32_t chk, const ScreenRow& st) {
+    return (st.tie | __ballot(chk >= 0u - (kScreenZone << 9))) != 0;
+}
+
 // Wavefronts per SIMD the register allocation aims for: the logits of NC chunks
 // take 8 NC registers per lane.
 constexpr int lis_waves_per_simd(int NC) { return NC <= 8 ? 3 : (NC <= 12 ? 2 : 1); }
@@ -590,6 +688,123 @@ __device__ __forceinline__ RowState tile_iexp(int (&lg)[NC][8], uint32_t (&zb)[N
         st.rs = row_sum(sum, k);
     }
     return st;
+}
+
+// The exact row state from S 2^-n, the sum of the e bits' values.
+__device__ __forceinline__ RowState screen_exact(double S, const LisConsts& k) {
+    const double S2 = ldexp(S, k.n + 1);
+    RowState st;
+    st.S2s = S2 * kCodeScale;
+    st.sc = kCodeScale;
+    asm volatile("" : "+s"(st.sc));
+    st.tau = third_floor_f32(S2);
+    return st;
+}
+
+// Screened form of tile_iexp: lg holds the e bits afterwards (0 for masked
+// keys of the last chunk).  EXACT: the row sum S is exact (every key added in
+// binary64, 5 cycles more a key); kernels that overwrite a chunk's e before the
+// last chunk is decided need it, the others take the sum again (screen_sum)
+// when a chunk is undecided.
+template <int NC, int NT, bool EXACT, bool P0 = false>
+__device__ __forceinline__ ScreenRow tile_iexp_screen(int (&lg)[NC][8], const LisConsts& k,
+                                                      double& S) {
+    const int32_t mc = screen_c(tile_max<NC>(lg), k);
+    double part[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        float e[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (c == NC - 1 && t >= NT) {
+                e[t] = 0.0f;
+                continue;
+            }
+            const int v = lg[c][t];
+            uint32_t b = screen_iexp<P0>(v, mc, k);
+            if (c == NC - 1) b = v != INT_MIN ? b : 0u;
+            lg[c][t] = (int)b;
+            e[t] = __uint_as_float(b);
+            if (EXACT) part[t & 3] += (double)e[t];
+        }
+        if (!EXACT)
+            part[c & 1] += (double)(((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7])));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    S = row4_sum((part[0] + part[1]) + (part[2] + part[3]));
+    return screen_row(S, k);
+}
+
+// The exact S 2^-n from the e bits of a tile (cold: kept behind its branch).
+template <int NC, int NT>
+__device__ __forceinline__ double screen_sum(const int (&lg)[NC][8]) {
+    double part[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+#pragma unroll
+        for (int t = 0; t < (c < NC - 1 ? 8 : NT); ++t) {
+            int eb = lg[c][t];
+            asm volatile("" : "+v"(eb));
+            part[t & 3] += (double)__int_as_float(eb);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return row4_sum((part[0] + part[1]) + (part[2] + part[3]));
+}
+
+// bf16 operand of P = 2^(top - code) of chunk c (top <= 15) from the screened
+// codes; undecided: a key of the wavefront's chunk may be wrong.  A masked key's
+// P meets V = 0.
+template <int NC, int NT>
+__device__ __forceinline__ u32x4 chunk_pbits_screen(const int (&lg)[NC][8], const ScreenRow& st,
+                                                    int c, bool& undecided) {
+    u32x4 pb;
+    uint32_t chk = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if (c == NC - 1 && 2 * w >= NT) {
+            pb[w] = 0u;
+            continue;
+        }
+        const uint32_t b0 = screen_key((uint32_t)lg[c][2 * w], st);
+        const uint32_t b1 = screen_key((uint32_t)lg[c][2 * w + 1], st);
+        chk = max(max(chk, b0 << 9), b1 << 9);
+        // the exponent fields (4 bits) of both, plus the bias
+        pb[w] = (__builtin_amdgcn_perm(b1, b0, 0x07060302u) & 0x07800780u) + 0x3F803F80u;
+    }
+    undecided = screen_failed(chk, st);
+    return pb;
+}
+
+// The operand of a chunk by the binary64 form, from its e bits and S 2^-n.
+__device__ __forceinline__ u32x4 chunk_pbits_exact(const int (&e)[8], double S, const LisConsts& k) {
+    const RowState ex = screen_exact(S, k);
+    const uint32_t kr = ((uint32_t)(k.top + 1) << 25) - 1u;
+    uint32_t x[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] = 127u + code_rev_f(e[t] + (k.n << 23), ex, kr);
+    return u32x4{(x[0] | (x[1] << 16)) << 7, (x[2] | (x[3] << 16)) << 7,
+                 (x[4] | (x[5] << 16)) << 7, (x[6] | (x[7] << 16)) << 7};
+}
+
+// The same, one key at a time through 512 dwords of LDS that belong to the
+// wavefront (its S 2^-n follows them), so that the cold code needs few
+// registers.
+__device__ __forceinline__ u32x4 chunk_pbits_exact_lds(const int (&e)[8], const LisConsts& k,
+                                                       uint32_t* scr, int lane) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) scr[64 * t + lane] = (uint32_t)e[t];
+    const RowState ex = screen_exact(*reinterpret_cast<const double*>(scr + 512 + 2 * lane), k);
+    const uint32_t kr = ((uint32_t)(k.top + 1) << 25) - 1u;
+#pragma unroll 1
+    for (int t = 0; t < 8; ++t) {
+        const int eb = (int)scr[64 * t + lane] + (k.n << 23);
+        scr[64 * t + lane] = (127u + code_rev_f(eb, ex, kr)) << 7;
+    }
+    u32x4 pb;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) pb[w] = scr[128 * w + lane] | (scr[128 * w + 64 + lane] << 16);
+    return pb;
 }
 
 // Codes of chunk c; in the last chunk masked keys (held as 0) get code 0 and
@@ -743,6 +958,10 @@ __device__ __forceinline__ void store_out(const f32x4 (&acc)[DTMAX], const LisAr
 template <int DTMAX>
 constexpr int out_lds_dwords() { return 16 * (16 * DTMAX + 4); }
 
+// The unit kernel's LDS per wavefront: that block, or 640 dwords (an undecided
+// chunk's keys and the row sums) where it is smaller.
+constexpr int unit_lds_dwords(int dtm) { return 16 * (16 * dtm + 4) > 640 ? 16 * (16 * dtm + 4) : 640; }
+
 template <int DTMAX>
 __device__ __forceinline__ void store_out_rows(const f32x4 (&acc)[DTMAX], int32_t* ot,
                                                const LisArgs& a, int64_t g, int i0, int lane,
@@ -840,27 +1059,17 @@ __device__ __forceinline__ void tile_load(int (&lg)[NC][8], const RowPtrs& rp, i
 // share the remainder.  Float path only.  HALF: the last chunk holds at most
 // 16 keys and is contracted by the 16x16x16 MFMA.
 // ---------------------------------------------------------------------------
-// Prefetch of the next tile: its first PF chunks are requested right after
-// the I-Exp pass of the current tile, and chunk PF + c right after chunk c of
-// the current tile has gone through its MFMA (its registers are free by then),
-// so the next tile is in flight without holding two tiles in registers.
-// Rows of five or more chunks also defer the masking of the last chunk's keys
+// Prefetch of the next tile: chunk c is requested right after chunk c of the
+// current tile has gone through its MFMA (its registers are free by then), so
+// the next tile is in flight without holding two tiles in registers.
+// Fused rows of five or more chunks defer the masking of the last chunk's keys
 // past Lk to the chunk's use (mask_last): applied at the load, it made the
 // wavefront wait for the whole next tile right after requesting its last
-// chunk, before the current tile's output was stored.  Measured on the ViT-B/16
-// shapes (768 x 197 x 197, events over 96 launches, same box): deferred masking
-// with PF = 2 (156 VGPRs) 43.8-45.3 us against 45.4-46.9 us before; PF = 0 or 1
-// 44.5-45.3, PF = 3 45.6, PF = 4 48.1 (168 VGPRs, spills); requesting the last
-// chunk first no better than PF = 0.  The small-unit kernels keep the masking
-// at the load and PF = 0: deferred, they spill at their 80-register bound.
-// Both are taken by the fused kernels (the codes-only kernels of seven chunks
-// spill more with the deferred masking), PF = 2 where it fits the 168
-// registers of three wavefronts per SIMD: all but the widest (seven full
-// chunks and d > 32), which keeps PF = 0.
+// chunk, before the current tile's output was stored.  The small-unit kernels
+// keep the masking at the load: deferred, they spilled at their register bound.
+// Requesting one chunk of the next tile before the code pass made the screened
+// kernel spill (ViT-B/16, 768 x 197 x 197: 47.1 against 40.6 us).
 constexpr bool unit_defer(int NC, bool FUSED) { return FUSED && NC >= 5; }
-constexpr int unit_prefetch(int NC, bool FUSED, int DTMAX, bool HALF) {
-    return unit_defer(NC, FUSED) && !(NC == 7 && DTMAX == 4 && !HALF) ? 2 : 0;
-}
 
 template <int NC, bool HALF, bool DEFER = false>
 __device__ __forceinline__ void load_one_chunk(int (&lg)[NC][8], const RowPtrs& rp, int c, int kg,
@@ -952,7 +1161,6 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
                                           int32_t* ot, const UnitBase& ub, int64_t g, int tile,
                                           int ntl, int lane, int r, int kg, uint32_t valid) {
     constexpr int NT = HALF ? 4 : 8;
-    constexpr int PF = unit_prefetch(NC, FUSED, DTMAX, HALF);
     constexpr bool DF = unit_defer(NC, FUSED);
     const int i0 = 16 * tile;
     // Always prefetch (a conditional load would keep the stale buffer live
@@ -960,29 +1168,36 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
     // are read again.
     const int nt = tile + WPU < ntl ? tile + WPU : tile;
     const RowPtrs rn = unit_row<NC>(a, p, ub, min(16 * nt + r, a.Lq - 1));
-    uint32_t zb[NC][2];
     if (DF) mask_last<NC, NT>(cur, valid);
-    const RowState st = tile_iexp<NC, true, NT>(cur, zb, k);
-    tile_load<NC, HALF, 0, PF, DF>(nxt, rn, kg, a.Lk);
     if constexpr (FUSED) {
+        double S;
+        const ScreenRow st = tile_iexp_screen<NC, NT, true>(cur, k, S);
+        uint32_t* scr = reinterpret_cast<uint32_t*>(ot);
+        *reinterpret_cast<double*>(scr + 512 + 2 * lane) = S;
         f32x4 acc[DTMAX];
 #pragma unroll
         for (int dt = 0; dt < DTMAX; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const u32x4 pb = chunk_pbits<NC, true, NT>(cur, zb, st, k, c);
+            bool undecided;
+            u32x4 pb = chunk_pbits_screen<NC, NT>(cur, st, c, undecided);
+            if (__builtin_expect(undecided, 0)) pb = chunk_pbits_exact_lds(cur[c], k, scr, lane);
             if (HALF && c == NC - 1)
                 chunk_mfma<DTMAX, true>(acc, pb, vt, p.ld, c, r, kg);
             else
                 chunk_mfma<DTMAX, false>(acc, pb, vt, p.ld, c, r, kg);
-            if (PF + c < NC) load_one_chunk<NC, HALF, DF>(nxt, rn, PF + c, kg, a.Lk);
+            load_one_chunk<NC, HALF, DF>(nxt, rn, c, kg, a.Lk);
             // keep each chunk's V^T reads next to its MFMAs (hoisting them all
             // would take 4 DTMAX registers per chunk)
             __builtin_amdgcn_sched_barrier(0);
         }
         if (p.out_vec) store_out_rows<DTMAX>(acc, ot, a, g, i0, lane, r, kg);
         else store_out<DTMAX>(acc, a, g, i0, r, kg);
-    } else if (p.codes_ldw != 0) {
+        return;
+    }
+    uint32_t zb[NC][2];
+    const RowState st = tile_iexp<NC, true, NT>(cur, zb, k);
+    if (p.codes_ldw != 0) {
         // Dense code rows: the tile's rows are one contiguous span of the codes
         // tensor.  They are gathered in LDS at the span's offset from a dword
         // boundary (mis), then written as whole aligned dwords, the partial
@@ -998,7 +1213,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
             int code[8];
             chunk_codes<NC, true, NT>(code, cur, zb, st, k, c);
             if (i < a.Lq) store_codes_row(cl + mis + r * nbr, a.Lk, k.top, c, kg, code);
-            if (PF + c < NC) load_one_chunk<NC, HALF, DF>(nxt, rn, PF + c, kg, a.Lk);
+            load_one_chunk<NC, HALF, DF>(nxt, rn, c, kg, a.Lk);
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_wave_barrier();
@@ -1022,7 +1237,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
             int code[8];
             chunk_codes<NC, true, NT>(code, cur, zb, st, k, c);
             if (i < a.Lq) store_codes_row(crow, a.Lk, k.top, c, kg, code);
-            if (PF + c < NC) load_one_chunk<NC, HALF, DF>(nxt, rn, PF + c, kg, a.Lk);
+            load_one_chunk<NC, HALF, DF>(nxt, rn, c, kg, a.Lk);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -1060,7 +1275,8 @@ __global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, WPU
 
     StageRegs sr;
     if constexpr (FUSED)
-        stage_load<64 * WPU>(sr, a.v + g * (int64_t)a.Lk * a.d, a.Lk, a.d, DTMAX, 0, 32 * NC, p.vec_ok);
+        stage_load<64 * WPU>(sr, a.v + g * (int64_t)a.Lk * a.d, a.Lk, a.d, DTMAX, 0, 32 * NC, a.zp_v,
+                             p.vec_ok);
 
     UnitBase ub;
     ub.loff = g * a.Lq * (int64_t)a.Lk;
@@ -1081,7 +1297,7 @@ __global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, WPU
         __syncthreads();
     }
     // LDS per wavefront: the output transpose (fused) or the tile's code rows
-    int32_t* ot = FUSED ? reinterpret_cast<int32_t*>(smem + p.vt_bytes) + wave * out_lds_dwords<DTMAX>()
+    int32_t* ot = FUSED ? reinterpret_cast<int32_t*>(smem + p.vt_bytes) + wave * unit_lds_dwords(DTMAX)
                         : reinterpret_cast<int32_t*>(smem + wave * p.codes_ldw);
     while (tile < ntl) {
         unit_tile<NC, FUSED, DTMAX, HALF, WPU>(bufA, bufB, a, p, k, vt, ot, ub, g, tile, ntl, lane, r,
@@ -1133,7 +1349,7 @@ __global__ __launch_bounds__(kBlock, lis_waves_per_simd(NC)) void lis_kernel(Lis
     const int8_t* vg = FUSED ? a.v + g * (int64_t)Lk * a.d : nullptr;
 
     StageRegs sr;
-    if (FUSED) stage_load(sr, vg, Lk, a.d, p.ncg, 0, min(p.kb, NC * 32), p.vec_ok);
+    if (FUSED) stage_load(sr, vg, Lk, a.d, p.ncg, 0, min(p.kb, NC * 32), a.zp_v, p.vec_ok);
 
     int lg[NC][8];
     tile_load<NC, false>(lg, row_ptrs<NC>(a, p, g, i), kg, Lk);

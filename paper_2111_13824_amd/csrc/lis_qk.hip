@@ -26,7 +26,7 @@ hipError_t launch_lis_qk(const LisArgs& a, const QkInput& in, hipStream_t stream
     const bool half = a.Lk - 32 * (nc - 1) <= 16;
     // float path (and its I-Exp without the pre-shift where that is 0) or the
     // integer path
-    const int fp = a.k.fp_ok != 0 ? (a.k.pre == 0 ? 2 : 1) : 0;
+    const int fp = a.k.fp_ok != 0 ? (a.k.s_pre == 0 ? 2 : 1) : 0;
     const QkArgs qa{in.q, in.k, in.zp_q, in.zp_k};
     // rows beyond 7 chunks: logits recomputed per pass from K in LDS
     if (nc > 7) return launch_qk_long(in.dk, dt, fp, a, qa, p, lds, stream);

@@ -47,6 +47,177 @@ __device__ __forceinline__ int kst_off(int j, int u) {
     return j * DK + 16 * u;
 }
 
+// K of the unit into LDS (keys [0, kp), zeros past Lk), and each key's
+// zero-point term -zq sum_c k[j][c] (the initial accumulator of its logits).
+// The DK / 16 threads that load a key's 16-byte units are neighbours: their
+// partial sums meet by DPP in the same pass.  kp DK / 16 is a multiple of 64,
+// so a wavefront is all in or all out.
+template <int DK, int NTHREADS>
+__device__ __forceinline__ void stage_k(int8_t* kst, int32_t* ck, const int8_t* kg_base, int Lk,
+                                        int kp, int zq) {
+    static_assert(DK == 32 || DK == 64, "two or four lanes a key");
+    for (int w = threadIdx.x; w < kp * (DK / 16); w += NTHREADS) {
+        const int j = w / (DK / 16);
+        const int u = w - j * (DK / 16);
+        i32x4v val = {0, 0, 0, 0};
+        if (j < Lk) val = *reinterpret_cast<const i32x4v*>(kg_base + (int64_t)j * DK + 16 * u);
+        *reinterpret_cast<i32x4v*>(kst + kst_off<DK>(j, u)) = val;
+        int s = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s = __builtin_amdgcn_sdot4(val[q], 0x01010101, s, false);
+        s += __builtin_amdgcn_update_dpp(0, s, 0xB1, 0xF, 0xF, false);      // quad_perm 1,0,3,2
+        if constexpr (DK == 64)
+            s += __builtin_amdgcn_update_dpp(0, s, 0x4E, 0xF, 0xF, false);  // quad_perm 2,3,0,1
+        if (u == 0) ck[j] = -(zq * s);
+    }
+}
+
+// Logits of chunk c for lane (query r, group kg): keys 32 c + 4 kg + t
+// (t < 4) and 32 c + 16 + 4 kg + (t - 4), INT_MIN past Lk (only the last chunk
+// holds such keys); the bias row (if any) added.  The per-key zero-point
+// terms are the MFMA's initial accumulator (same layout: lane (r, kg) holds
+// keys j0 .. j0 + 3).  The per-query term zp_q zp_k dk - zp_k sum_c q[i][c] is
+// left out: the Log-Int-Softmax of a row depends only on the differences of
+// its logits.  HALF: the last chunk holds at most 16 keys.
+template <int DK, bool HALF>
+__device__ __forceinline__ void qk_chunk(int (&lg)[8], const int8_t* kst, const int32_t* ck,
+                                         const i32x4v (&qb)[DK >= 64 ? DK / 64 : 1], int64_t qb8,
+                                         const int32_t* brow, int c, int r, int kg, int Lk,
+                                         bool last) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (HALF && last && h == 1) {
+#pragma unroll
+            for (int t = 4; t < 8; ++t) lg[t] = INT_MIN;
+            continue;
+        }
+        const int kt = 2 * c + h;
+        const int key = 16 * kt + r;          // A operand row of this lane
+        const int j0 = 16 * kt + 4 * kg;      // keys of s[0..3]
+        i32x4v s = *reinterpret_cast<const i32x4v*>(ck + j0);
+        if constexpr (DK >= 64) {
+#pragma unroll
+            for (int m = 0; m < DK / 64; ++m) {
+                const i32x4v av = *reinterpret_cast<const i32x4v*>(kst + kst_off<DK>(key, 4 * m + kg));
+                s = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, qb[m], s, 0, 0, 0);
+            }
+        } else {
+            const int64_t av = *reinterpret_cast<const int64_t*>(kst + key * DK + 8 * kg);
+            s = __builtin_amdgcn_mfma_i32_16x16x32_i8(av, qb8, s, 0, 0, 0);
+        }
+        if (!last) {
+            if (brow) {
+                const i32x4a4 b = *reinterpret_cast<const i32x4a4*>(brow + j0);
+                s += i32x4v{b.x, b.y, b.z, b.w};
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) lg[4 * h + t] = s[t];
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bool ok = j0 + t < Lk;
+                lg[4 * h + t] = ok ? s[t] + (brow && ok ? brow[j0 + t] : 0) : INT_MIN;
+            }
+        }
+    }
+}
+
+// The query bytes of row i: the B operand of the logits' MFMA (DK / 4 bytes a
+// lane).
+template <int DK>
+__device__ __forceinline__ void qk_load_q(const int8_t* q_base, int i, int kg,
+                                          i32x4v (&dst)[DK >= 64 ? DK / 64 : 1], int64_t& dst8) {
+    const int8_t* qrow = q_base + (int64_t)i * DK;
+    if constexpr (DK >= 64) {
+#pragma unroll
+        for (int m = 0; m < DK / 64; ++m)
+            dst[m] = *reinterpret_cast<const i32x4v*>(qrow + 64 * m + 16 * kg);
+    } else {
+        dst8 = *reinterpret_cast<const int64_t*>(qrow + 8 * kg);
+    }
+}
+
+// One 16-query tile in three passes over the keys, the logits recomputed in
+// each: the row maximum, the exact I-Exp sum, and the codes with the product
+// P V.  The chunk count is a run-time value; masked keys get P = 0.
+template <int DTMAX, bool FP, int DK, bool P0>
+__device__ __forceinline__ void qk_tile_passes(f32x4 (&acc)[DTMAX], const int8_t* kst,
+                                               const int32_t* ck, const uint16_t* vt, int ld,
+                                               const i32x4v (&qb)[DK >= 64 ? DK / 64 : 1],
+                                               int64_t qb8, const int32_t* brow,
+                                               const LisConsts& k, int nc, int Lk, int r, int kg) {
+    int mx = INT_MIN;
+#pragma unroll 1
+    for (int c = 0; c < nc; ++c) {
+        int lg[8];
+        qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) mx = max(mx, lg[t]);
+    }
+    mx = row4_max(mx);
+
+    RowState st;
+    if constexpr (FP) {
+        double part[2] = {0.0, 0.0};
+#pragma unroll 1
+        for (int c = 0; c < nc; ++c) {
+            int lg[8];
+            qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const float e = iexp_f<P0>(lg[t], mx, k);
+                part[t & 1] += lg[t] != INT_MIN ? (double)e : 0.0;
+            }
+        }
+        const double S2 = 2.0 * row4_sum(part[0] + part[1]);
+        st.S2s = S2 * kCodeScale;
+        st.sc = kCodeScale;
+        asm volatile("" : "+s"(st.sc));
+        st.tau = third_floor_f32(S2);
+    } else {
+        uint64_t sum = 0;
+#pragma unroll 1
+        for (int c = 0; c < nc; ++c) {
+            int lg[8];
+            qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                uint32_t z;
+                const uint32_t qL = iexp_qL(lg[t], mx, k, z);
+                sum += lg[t] != INT_MIN ? ((uint64_t)qL << (k.n - (int)z)) : 0ull;
+            }
+        }
+        st.rs = row_sum(sum, k);
+    }
+
+    const uint32_t kr = ((uint32_t)(k.top + 1) << 25) - 1u;
+    const int ptop = (127 + k.top) << 7;
+#pragma unroll
+    for (int dt = 0; dt < DTMAX; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int c = 0; c < nc; ++c) {
+        int lg[8];
+        qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
+        uint32_t pbits[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const bool valid = lg[t] != INT_MIN;
+            if constexpr (FP) {
+                const int eb = __float_as_int(iexp_f<P0>(valid ? lg[t] : mx, mx, k));
+                pbits[t] = valid ? (127u + code_rev_f(eb, st, kr)) << 7 : 0u;
+            } else {
+                uint32_t z;
+                const uint32_t qL = iexp_qL(valid ? lg[t] : mx, mx, k, z);
+                const int cd = lis_code(qL, z, st.rs, k);
+                pbits[t] = valid ? (uint32_t)(ptop - (cd << 7)) : 0u;
+            }
+        }
+        const u32x4 pb = {pbits[0] | (pbits[1] << 16), pbits[2] | (pbits[3] << 16),
+                          pbits[4] | (pbits[5] << 16), pbits[6] | (pbits[7] << 16)};
+        chunk_mfma<DTMAX, false, true>(acc, pb, vt, ld, c, r, kg);
+    }
+}
+
 template <int NC, int DTMAX, bool HALF, bool FP, int DK, bool P0 = false>
 __global__ __launch_bounds__(kBlock, 3) void lis_qk_kernel(LisArgs a, QkArgs qa, LisLaunch p) {
     constexpr int NT = HALF ? 4 : 8;
@@ -68,122 +239,66 @@ __global__ __launch_bounds__(kBlock, 3) void lis_qk_kernel(LisArgs a, QkArgs qa,
 
     // V^T and K of the unit into LDS
     StageRegs sr;
-    stage_load(sr, a.v + g * (int64_t)a.Lk * a.d, a.Lk, a.d, DTMAX, 0, KP, p.vec_ok);
+    stage_load(sr, a.v + g * (int64_t)a.Lk * a.d, a.Lk, a.d, DTMAX, 0, KP, a.zp_v, p.vec_ok);
     const int8_t* kg_base = qa.k + g * (int64_t)a.Lk * DK;
-    for (int w = threadIdx.x; w < KP * (DK / 16); w += kBlock) {
-        const int j = w / (DK / 16);
-        const int u = w - j * (DK / 16);
-        i32x4v val = {0, 0, 0, 0};
-        if (j < a.Lk) val = *reinterpret_cast<const i32x4v*>(kg_base + (int64_t)j * DK + 16 * u);
-        *reinterpret_cast<i32x4v*>(kst + kst_off<DK>(j, u)) = val;
-    }
+    stage_k<DK, kBlock>(kst, ck, kg_base, a.Lk, KP, qa.zq);
     stage_store(sr, vt, p.ld, DTMAX, KP, a.zp_v);
-    __syncthreads();
-    // per-key zero-point term zq sum_c k[j][c] (0 for padded keys, whose
-    // logits are masked anyway)
-    if (threadIdx.x < KP) {
-        const int j = threadIdx.x;
-        int s = 0;
-#pragma unroll
-        for (int u = 0; u < DK / 16; ++u) {
-            const i32x4v v = *reinterpret_cast<const i32x4v*>(kst + kst_off<DK>(j, u));
-            s = __builtin_amdgcn_sdot4(v.x, 0x01010101, s, false);
-            s = __builtin_amdgcn_sdot4(v.y, 0x01010101, s, false);
-            s = __builtin_amdgcn_sdot4(v.z, 0x01010101, s, false);
-            s = __builtin_amdgcn_sdot4(v.w, 0x01010101, s, false);
-        }
-        ck[j] = -(qa.zq * s);        // stored negated: the initial accumulator of the logits
-    }
     __syncthreads();
 
     const int8_t* q_base = qa.q + g * (int64_t)a.Lq * DK;
     const int32_t* bplane = a.bias ? a.bias + (g % a.Hb) * (int64_t)a.Lq * a.Lk : nullptr;
 
-    // B operand: this lane's bytes of query row i (DK / 4 bytes)
     i32x4v qb[DK >= 64 ? DK / 64 : 1];
     int64_t qb8 = 0;
-    auto load_q = [&](int t, i32x4v (&dst)[DK >= 64 ? DK / 64 : 1], int64_t& dst8) {
-        const int8_t* qrow = q_base + (int64_t)min(16 * t + r, a.Lq - 1) * DK;
-        if constexpr (DK >= 64) {
-#pragma unroll
-            for (int m = 0; m < DK / 64; ++m)
-                dst[m] = *reinterpret_cast<const i32x4v*>(qrow + 64 * m + 16 * kg);
-        } else {
-            dst8 = *reinterpret_cast<const int64_t*>(qrow + 8 * kg);
-        }
-    };
     int tile = (wave + (int)(g & 3)) & 3;
-    if (tile < p.ntiles) load_q(tile, qb, qb8);
+    if (tile < p.ntiles) qk_load_q<DK>(q_base, min(16 * tile + r, a.Lq - 1), kg, qb, qb8);
     for (; tile < p.ntiles; tile += 4) {
         const int i0 = 16 * tile;
         const int i = min(i0 + r, a.Lq - 1);
 
-        // logits of this tile in the Log-Int-Softmax lane layout
+        // logits of this tile in the Log-Int-Softmax lane layout, with or
+        // without a bias (uniform; two bodies, since one that adds the bias
+        // under a branch copies every logit)
         int lg[NC][8];
+        auto logits = [&](const int32_t* brow) __attribute__((always_inline)) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (HALF && c == NC - 1 && h == 1) {
-#pragma unroll
-                    for (int t = 4; t < 8; ++t) lg[c][t] = INT_MIN;
-                    continue;
-                }
-                const int kt = 2 * c + h;
-                const int key = 16 * kt + r;          // A operand row of this lane
-                const int j0 = 16 * kt + 4 * kg;      // keys of s[0..3]
-                // the per-key zero-point terms enter as the accumulator's
-                // initial value (same layout: lane (r, kg) holds keys j0 ..
-                // j0 + 3), so the sum needs no separate add
-                i32x4v s = *reinterpret_cast<const i32x4v*>(ck + j0);
-                if constexpr (DK >= 64) {
-#pragma unroll
-                    for (int m = 0; m < DK / 64; ++m) {
-                        const i32x4v av =
-                            *reinterpret_cast<const i32x4v*>(kst + kst_off<DK>(key, 4 * m + kg));
-                        s = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, qb[m], s, 0, 0, 0);
-                    }
-                } else {
-                    const int64_t av = *reinterpret_cast<const int64_t*>(kst + key * DK + 8 * kg);
-                    s = __builtin_amdgcn_mfma_i32_16x16x32_i8(av, qb8, s, 0, 0, 0);
-                }
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    // the per-query term zp_q zp_k dk - zp_k sum_c q[i][c] is
-                    // left out: the Log-Int-Softmax of a row depends only on
-                    // the differences of its logits (u = max - v)
-                    const int v = s[t];
-                    // only the last chunk can hold keys past Lk
-                    lg[c][4 * h + t] = (c < NC - 1 || j0 + t < a.Lk) ? v : INT_MIN;
-                }
-            }
-        }
+            for (int c = 0; c < NC; ++c)
+                qk_chunk<DK, HALF>(lg[c], kst, ck, qb, qb8, brow, c, r, kg, a.Lk, c == NC - 1);
+        };
+        if (bplane) logits(bplane + (int64_t)i * a.Lk);
+        else logits(nullptr);
         // the next tile's query bytes, in flight during the rest of this tile
-        load_q(tile + 4 < p.ntiles ? tile + 4 : tile, qb, qb8);
-        if (bplane) {   // uniform: the bias of the lane's row, in a pass of its own
-            const int32_t* brow = bplane + (int64_t)i * a.Lk;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int j = 32 * c + 4 * kg + (t < 4 ? t : 12 + t);
-                    if (c < NC - 1 || j < a.Lk) lg[c][t] += brow[j];
-                }
-            }
-        }
-        uint32_t zb[NC][2];
-        const RowState st = tile_iexp<NC, FP, NT, P0>(lg, zb, k);
+        qk_load_q<DK>(q_base, min(16 * (tile + 4 < p.ntiles ? tile + 4 : tile) + r, a.Lq - 1), kg, qb, qb8);
         f32x4 acc[DTMAX];
 #pragma unroll
         for (int dt = 0; dt < DTMAX; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (FP) {
+            double S;
+            const ScreenRow st = tile_iexp_screen<NC, NT, false, P0>(lg, k, S);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const u32x4 pb = chunk_pbits<NC, FP, NT>(lg, zb, st, k, c);
-            if (HALF && c == NC - 1)
-                chunk_mfma<DTMAX, true, true>(acc, pb, vt, p.ld, c, r, kg);
-            else
-                chunk_mfma<DTMAX, false, true>(acc, pb, vt, p.ld, c, r, kg);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int c = 0; c < NC; ++c) {
+                bool undecided;
+                u32x4 pb = chunk_pbits_screen<NC, NT>(lg, st, c, undecided);
+                if (__builtin_expect(undecided, 0))
+                    pb = chunk_pbits_exact(lg[c], screen_sum<NC, NT>(lg), k);
+                if (HALF && c == NC - 1)
+                    chunk_mfma<DTMAX, true, true>(acc, pb, vt, p.ld, c, r, kg);
+                else
+                    chunk_mfma<DTMAX, false, true>(acc, pb, vt, p.ld, c, r, kg);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            uint32_t zb[NC][2];
+            const RowState st = tile_iexp<NC, FP, NT, P0>(lg, zb, k);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const u32x4 pb = chunk_pbits<NC, FP, NT>(lg, zb, st, k, c);
+                if (HALF && c == NC - 1)
+                    chunk_mfma<DTMAX, true, true>(acc, pb, vt, p.ld, c, r, kg);
+                else
+                    chunk_mfma<DTMAX, false, true>(acc, pb, vt, p.ld, c, r, kg);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         store_out_t<DTMAX>(acc, a, g, i0, r, kg, p.out_vec);
     }

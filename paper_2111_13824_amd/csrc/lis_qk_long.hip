@@ -20,43 +20,6 @@ namespace lis {
 constexpr int kQkLongWaves = 12;
 constexpr int kQkLongBlock = 64 * kQkLongWaves;
 
-// Logits of chunk c for lane (query r, group kg): keys 32 c + 4 kg + t
-// (t < 4) and 32 c + 16 + 4 kg + (t - 4), INT_MIN past Lk; the bias row (if
-// any) added.
-template <int DK>
-__device__ __forceinline__ void qk_long_chunk(int (&lg)[8], const int8_t* kst, const int32_t* ck,
-                                              const i32x4v (&qb)[DK >= 64 ? DK / 64 : 1],
-                                              int64_t qb8, const int32_t* brow, int c, int r, int kg,
-                                              int Lk) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int kt = 2 * c + h;
-        const int key = 16 * kt + r;
-        const int j0 = 16 * kt + 4 * kg;
-        // the per-key zero-point terms as the initial accumulator
-        i32x4v s = *reinterpret_cast<const i32x4v*>(ck + j0);
-        if constexpr (DK >= 64) {
-#pragma unroll
-            for (int m = 0; m < DK / 64; ++m) {
-                const i32x4v av = *reinterpret_cast<const i32x4v*>(kst + kst_off<DK>(key, 4 * m + kg));
-                s = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, qb[m], s, 0, 0, 0);
-            }
-        } else {
-            const int64_t av = *reinterpret_cast<const int64_t*>(kst + key * DK + 8 * kg);
-            s = __builtin_amdgcn_mfma_i32_16x16x32_i8(av, qb8, s, 0, 0, 0);
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) lg[4 * h + t] = j0 + t < Lk ? s[t] : INT_MIN;
-    }
-    if (brow) {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int j = 32 * c + 4 * kg + (t < 4 ? t : 12 + t);
-            if (j < Lk) lg[t] += brow[j];
-        }
-    }
-}
-
 template <int DTMAX, bool FP, int DK, bool P0 = false>
 __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, QkArgs qa,
                                                                    LisLaunch p) {
@@ -82,26 +45,7 @@ __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, Qk
     long_stage_vt<DTMAX, kQkLongBlock>(vt, p.ld, a.v + g * (int64_t)Lk * a.d, Lk, a.d, kp, a.zp_v,
                                        p.vec_ok);
     const int8_t* kg_base = qa.k + g * (int64_t)Lk * DK;
-    for (int w = threadIdx.x; w < kp * (DK / 16); w += kQkLongBlock) {
-        const int j = w / (DK / 16);
-        const int u = w - j * (DK / 16);
-        i32x4v val = {0, 0, 0, 0};
-        if (j < Lk) val = *reinterpret_cast<const i32x4v*>(kg_base + (int64_t)j * DK + 16 * u);
-        *reinterpret_cast<i32x4v*>(kst + kst_off<DK>(j, u)) = val;
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j < kp; j += kQkLongBlock) {
-        int s = 0;
-#pragma unroll
-        for (int u = 0; u < DK / 16; ++u) {
-            const i32x4v v = *reinterpret_cast<const i32x4v*>(kst + kst_off<DK>(j, u));
-            s = __builtin_amdgcn_sdot4(v.x, 0x01010101, s, false);
-            s = __builtin_amdgcn_sdot4(v.y, 0x01010101, s, false);
-            s = __builtin_amdgcn_sdot4(v.z, 0x01010101, s, false);
-            s = __builtin_amdgcn_sdot4(v.w, 0x01010101, s, false);
-        }
-        ck[j] = -(qa.zq * s);     // the per-key zero-point term, stored negated
-    }
+    stage_k<DK, kQkLongBlock>(kst, ck, kg_base, Lk, kp, qa.zq);
     __syncthreads();
 
     const int8_t* q_base = qa.q + g * (int64_t)a.Lq * DK;
@@ -129,7 +73,7 @@ __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, Qk
 #pragma unroll 1
         for (int c = 0; c < nc; ++c) {
             int lg[8];
-            qk_long_chunk<DK>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk);
+            qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
 #pragma unroll
             for (int t = 0; t < 8; ++t) mx = max(mx, lg[t]);
         }
@@ -141,7 +85,7 @@ __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, Qk
 #pragma unroll 1
             for (int c = 0; c < nc; ++c) {
                 int lg[8];
-                qk_long_chunk<DK>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk);
+                qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
                     const float e = iexp_f<P0>(lg[t], mx, k);
@@ -158,7 +102,7 @@ __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, Qk
 #pragma unroll 1
             for (int c = 0; c < nc; ++c) {
                 int lg[8];
-                qk_long_chunk<DK>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk);
+                qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
                     uint32_t z;
@@ -175,7 +119,7 @@ __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, Qk
 #pragma unroll 1
         for (int c = 0; c < nc; ++c) {
             int lg[8];
-            qk_long_chunk<DK>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk);
+            qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
             uint32_t pbits[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
