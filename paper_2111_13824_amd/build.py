@@ -14,8 +14,9 @@ LIB = os.path.join(HERE, "libfqvit.so")
 SOURCES = ["ptf_layernorm.hip", "lis_attention.hip", "lis_inst_lo.hip", "lis_inst_hi.hip",
            "lis_inst_unit.hip", "ptf_quant.hip", "lis_qk.hip", "lis_qk_dk32.hip",
            "lis_qk_dk64.hip", "lis_long_lo.hip", "lis_long_hi.hip",
-           "lis_qk_long.hip", "lis_attn_v.hip",
-           "fqvit_abi.cpp"]
+           "lis_qk_long.hip", "lis_qk_long_dk32.hip", "lis_qk_long_dk64.hip",
+           "lis_qk_long_dk32.hip:FQ_QK_HI", "lis_qk_long_dk64.hip:FQ_QK_HI", "lis_attn_v.hip",
+           "fqvit_abi.cpp"]     # "file:MACRO": compiled with -DMACRO
 OBJDIR = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -44,9 +45,10 @@ def build(verbose: bool = False) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
     cflags = [f for f in FLAGS if f != "-shared"]
-    objs = [os.path.join(OBJDIR, s + ".o") for s in SOURCES]
-    jobs = [[HIPCC, *cflags, *inc, "-c", os.path.join(CSRC, s), "-o", o]
-            for s, o in zip(SOURCES, objs)]
+    units = [s.partition(":") for s in SOURCES]
+    objs = [os.path.join(OBJDIR, f + m + ".o") for f, _, m in units]
+    jobs = [[HIPCC, *cflags, *(["-D" + m] if m else []), *inc, "-c", os.path.join(CSRC, f), "-o", o]
+            for (f, _, m), o in zip(units, objs)]
     workers = min(len(jobs), max(1, min(8, os.cpu_count() or 1)))
     with concurrent.futures.ThreadPoolExecutor(workers) as ex:
         list(ex.map(lambda c: _run(c, verbose), jobs))

@@ -355,6 +355,7 @@ struct LisLaunch {
     int64_t n_logits;  // elements of the logits tensor (G Lq Lk)
     int64_t n_bias;    // elements of the bias tensor (Hb Lq Lk), 0 without bias
     int tab_bytes;     // long-row kernel: LDS bytes of the I-Exp table (multiple of 16)
+    int split;         // workgroups per unit (unit, long-row and Q K kernels)
     int codes_ldw;     // unit kernel, codes only: LDS bytes per wavefront of the tile's
                        // code rows (dense rows, ld_codes = row bytes), 0: direct stores
 };
@@ -548,6 +549,7 @@ struct ScreenRow {
     float Xs;       // 4 S / 3 2^-T, biased up
     float tau;      // 2 S / 3 (scaled by 2^-n), biased up by more than its error
     float c;        // 2 / 3 2^-T, rounded up (uniform)
+    int32_t mc;     // screen_c of the row
     uint64_t tie;   // lanes whose row has X / 2 too close to e0 to tell (uniform)
 };
 
@@ -720,7 +722,8 @@ __device__ __forceinline__ ScreenRow tile_iexp_screen(int (&lg)[NC][8], const Li
                 e[t] = 0.0f;
                 continue;
             }
-            const int v = lg[c][t];
+            int v = lg[c][t];
+            if (NC > 7) asm volatile("" : "+v"(v));      // as in chunk_pbits_screen
             uint32_t b = screen_iexp<P0>(v, mc, k);
             if (c == NC - 1) b = v != INT_MIN ? b : 0u;
             lg[c][t] = (int)b;
@@ -732,7 +735,9 @@ __device__ __forceinline__ ScreenRow tile_iexp_screen(int (&lg)[NC][8], const Li
         __builtin_amdgcn_sched_barrier(0);
     }
     S = row4_sum((part[0] + part[1]) + (part[2] + part[3]));
-    return screen_row(S, k);
+    ScreenRow st = screen_row(S, k);
+    st.mc = mc;
+    return st;
 }
 
 // The exact S 2^-n from the e bits of a tile (cold: kept behind its branch).
@@ -754,8 +759,10 @@ __device__ __forceinline__ double screen_sum(const int (&lg)[NC][8]) {
 
 // bf16 operand of P = 2^(top - code) of chunk c (top <= 15) from the screened
 // codes; undecided: a key of the wavefront's chunk may be wrong.  A masked key's
-// P meets V = 0.
-template <int NC, int NT>
+// P meets V = 0.  HOLD: an empty asm keeps the chunk's arithmetic in its place
+// (free of side effects, the compiler would start every chunk's at once, and
+// spill, where no branch separates the chunks).
+template <int NC, int NT, bool HOLD>
 __device__ __forceinline__ u32x4 chunk_pbits_screen(const int (&lg)[NC][8], const ScreenRow& st,
                                                     int c, bool& undecided) {
     u32x4 pb;
@@ -766,8 +773,10 @@ __device__ __forceinline__ u32x4 chunk_pbits_screen(const int (&lg)[NC][8], cons
             pb[w] = 0u;
             continue;
         }
-        const uint32_t b0 = screen_key((uint32_t)lg[c][2 * w], st);
-        const uint32_t b1 = screen_key((uint32_t)lg[c][2 * w + 1], st);
+        uint32_t e0 = (uint32_t)lg[c][2 * w], e1 = (uint32_t)lg[c][2 * w + 1];
+        if (HOLD) asm volatile("" : "+v"(e0), "+v"(e1));
+        const uint32_t b0 = screen_key(e0, st);
+        const uint32_t b1 = screen_key(e1, st);
         chk = max(max(chk, b0 << 9), b1 << 9);
         // the exponent fields (4 bits) of both, plus the bias
         pb[w] = (__builtin_amdgcn_perm(b1, b0, 0x07060302u) & 0x07800780u) + 0x3F803F80u;
@@ -785,6 +794,25 @@ __device__ __forceinline__ u32x4 chunk_pbits_exact(const int (&e)[8], double S, 
     for (int t = 0; t < 8; ++t) x[t] = 127u + code_rev_f(e[t] + (k.n << 23), ex, kr);
     return u32x4{(x[0] | (x[1] << 16)) << 7, (x[2] | (x[3] << 16)) << 7,
                  (x[4] | (x[5] << 16)) << 7, (x[6] | (x[7] << 16)) << 7};
+}
+
+// What the exact codes of an undecided chunk add to the screened ones, as a
+// bf16 operand: every screened P is the exact one or half of it, so the
+// difference is 0 or the screened P itself (and no partial sum of the product
+// leaves the exact one's bounds).  lg: the chunk's logits (INT_MIN masked).
+template <bool P0>
+__device__ __forceinline__ u32x4 chunk_pbits_diff(const int (&lg)[8], const ScreenRow& st,
+                                                  const RowState& ex, const LisConsts& k) {
+    const uint32_t kr = ((uint32_t)(k.top + 1) << 25) - 1u;
+    uint32_t x[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const uint32_t eb = screen_iexp<P0>(lg[t], st.mc, k);
+        const uint32_t xs = screen_key(eb, st) >> 23;
+        const uint32_t xe = code_rev_f((int)(eb + ((uint32_t)k.n << 23)), ex, kr);
+        x[t] = lg[t] != INT_MIN && xe > xs ? (127u + xs) << 7 : 0u;
+    }
+    return u32x4{x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16)};
 }
 
 // The same, one key at a time through 512 dwords of LDS that belong to the
@@ -1059,17 +1087,19 @@ __device__ __forceinline__ void tile_load(int (&lg)[NC][8], const RowPtrs& rp, i
 // share the remainder.  Float path only.  HALF: the last chunk holds at most
 // 16 keys and is contracted by the 16x16x16 MFMA.
 // ---------------------------------------------------------------------------
-// Prefetch of the next tile: chunk c is requested right after chunk c of the
-// current tile has gone through its MFMA (its registers are free by then), so
-// the next tile is in flight without holding two tiles in registers.
+// Prefetch of the next tile: its first PF chunks are requested right after
+// the I-Exp pass of the current tile, and chunk PF + c right after chunk c of
+// the current tile has gone through its MFMA (its registers are free by then),
+// so the next tile is in flight without holding two tiles in registers.
 // Fused rows of five or more chunks defer the masking of the last chunk's keys
 // past Lk to the chunk's use (mask_last): applied at the load, it made the
 // wavefront wait for the whole next tile right after requesting its last
 // chunk, before the current tile's output was stored.  The small-unit kernels
 // keep the masking at the load: deferred, they spilled at their register bound.
-// Requesting one chunk of the next tile before the code pass made the screened
-// kernel spill (ViT-B/16, 768 x 197 x 197: 47.1 against 40.6 us).
 constexpr bool unit_defer(int NC, bool FUSED) { return FUSED && NC >= 5; }
+constexpr int unit_prefetch(int NC, bool FUSED, int DTMAX, bool HALF) {
+    return unit_defer(NC, FUSED) && !(NC == 7 && DTMAX == 4 && !HALF) ? 2 : 0;
+}
 
 template <int NC, bool HALF, bool DEFER = false>
 __device__ __forceinline__ void load_one_chunk(int (&lg)[NC][8], const RowPtrs& rp, int c, int kg,
@@ -1161,6 +1191,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
                                           int32_t* ot, const UnitBase& ub, int64_t g, int tile,
                                           int ntl, int lane, int r, int kg, uint32_t valid) {
     constexpr int NT = HALF ? 4 : 8;
+    constexpr int PF = unit_prefetch(NC, FUSED, DTMAX, HALF);
     constexpr bool DF = unit_defer(NC, FUSED);
     const int i0 = 16 * tile;
     // Always prefetch (a conditional load would keep the stale buffer live
@@ -1172,6 +1203,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
     if constexpr (FUSED) {
         double S;
         const ScreenRow st = tile_iexp_screen<NC, NT, true>(cur, k, S);
+        tile_load<NC, HALF, 0, PF, DF>(nxt, rn, kg, a.Lk);
         uint32_t* scr = reinterpret_cast<uint32_t*>(ot);
         *reinterpret_cast<double*>(scr + 512 + 2 * lane) = S;
         f32x4 acc[DTMAX];
@@ -1180,13 +1212,13 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             bool undecided;
-            u32x4 pb = chunk_pbits_screen<NC, NT>(cur, st, c, undecided);
+            u32x4 pb = chunk_pbits_screen<NC, NT, true>(cur, st, c, undecided);
             if (__builtin_expect(undecided, 0)) pb = chunk_pbits_exact_lds(cur[c], k, scr, lane);
             if (HALF && c == NC - 1)
                 chunk_mfma<DTMAX, true>(acc, pb, vt, p.ld, c, r, kg);
             else
                 chunk_mfma<DTMAX, false>(acc, pb, vt, p.ld, c, r, kg);
-            load_one_chunk<NC, HALF, DF>(nxt, rn, c, kg, a.Lk);
+            if (PF + c < NC) load_one_chunk<NC, HALF, DF>(nxt, rn, PF + c, kg, a.Lk);
             // keep each chunk's V^T reads next to its MFMAs (hoisting them all
             // would take 4 DTMAX registers per chunk)
             __builtin_amdgcn_sched_barrier(0);
@@ -1197,6 +1229,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
     }
     uint32_t zb[NC][2];
     const RowState st = tile_iexp<NC, true, NT>(cur, zb, k);
+    tile_load<NC, HALF, 0, PF, DF>(nxt, rn, kg, a.Lk);
     if (p.codes_ldw != 0) {
         // Dense code rows: the tile's rows are one contiguous span of the codes
         // tensor.  They are gathered in LDS at the span's offset from a dword
@@ -1213,7 +1246,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
             int code[8];
             chunk_codes<NC, true, NT>(code, cur, zb, st, k, c);
             if (i < a.Lq) store_codes_row(cl + mis + r * nbr, a.Lk, k.top, c, kg, code);
-            load_one_chunk<NC, HALF, DF>(nxt, rn, c, kg, a.Lk);
+            if (PF + c < NC) load_one_chunk<NC, HALF, DF>(nxt, rn, PF + c, kg, a.Lk);
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_wave_barrier();
@@ -1237,7 +1270,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
             int code[8];
             chunk_codes<NC, true, NT>(code, cur, zb, st, k, c);
             if (i < a.Lq) store_codes_row(crow, a.Lk, k.top, c, kg, code);
-            load_one_chunk<NC, HALF, DF>(nxt, rn, c, kg, a.Lk);
+            if (PF + c < NC) load_one_chunk<NC, HALF, DF>(nxt, rn, PF + c, kg, a.Lk);
             __builtin_amdgcn_sched_barrier(0);
         }
     }

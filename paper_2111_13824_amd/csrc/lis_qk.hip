@@ -1,9 +1,12 @@
 // Host side of the integer-only attention from int8 Q and K (kernels in
-// lis_qk_kernel.h and lis_qk_long.hip): launch geometry and LDS of one
-// workgroup per unit.
+// lis_qk_kernel.h and lis_qk_long.hip): launch geometry and LDS.
+#include <algorithm>
+
 #include "lis_qk_kernel.h"
 
 namespace fqvit {
+
+constexpr size_t kQkLds = 160 * 1024;     // LDS of a CU
 
 hipError_t launch_lis_qk(const LisArgs& a, const QkInput& in, hipStream_t stream) {
     using namespace lis;
@@ -28,8 +31,26 @@ hipError_t launch_lis_qk(const LisArgs& a, const QkInput& in, hipStream_t stream
     // integer path
     const int fp = a.k.fp_ok != 0 ? (a.k.s_pre == 0 ? 2 : 1) : 0;
     const QkArgs qa{in.q, in.k, in.zp_q, in.zp_k};
-    // rows beyond 7 chunks: logits recomputed per pass from K in LDS
-    if (nc > 7) return launch_qk_long(in.dk, dt, fp, a, qa, p, lds, stream);
+    // Workgroups per unit.  A workgroup's time is its staging plus its
+    // wavefronts' tiles one after the other, so where the units alone do not
+    // fill the workgroup slots of 256 CUs (by LDS), a unit is dealt to as many
+    // as do, at most one tile a wavefront.  Measured on one MI355X: 75 units of
+    // 197 x 197, dk = d = 32 (with the requantization) 20.7 us undivided, 13.0
+    // us divided; one DeiT-T block (LayerNorm, 3 units of 197 x 197,
+    // requantization) 22.0 and 13.6 us; 24 units of 577 x 577 on the integer
+    // path 205 and 78 us.
+    const bool lng = nc > kQkRegsNC;
+    const int waves = lng && fp == 0 ? kQkLongWaves : qk_waves(nc);
+    const int64_t slots = 256 * std::max<int64_t>(1, std::min<int64_t>(12 / waves, kQkLds / lds));
+    const int64_t most = (p.ntiles + waves - 1) / waves;
+    p.split = (int)std::max<int64_t>(1, std::min<int64_t>(most, slots / a.G));
+    if (lng && fp == 0) return launch_qk_long_int(in.dk, dt, a, qa, p, lds, stream);
+    if (lng && in.dk == 32)
+        return nc <= 14 ? launch_qk_long32_lo(nc, dt, fp, a, qa, p, lds, stream)
+                        : launch_qk_long32_hi(nc, dt, fp, a, qa, p, lds, stream);
+    if (lng)
+        return nc <= 14 ? launch_qk_long64_lo(nc, dt, fp, a, qa, p, lds, stream)
+                        : launch_qk_long64_hi(nc, dt, fp, a, qa, p, lds, stream);
     if (in.dk == 32) return launch_qk_dk32(nc, dt, half, fp, a, qa, p, lds, stream);
     return launch_qk_dk64(nc, dt, half, fp, a, qa, p, lds, stream);
 }

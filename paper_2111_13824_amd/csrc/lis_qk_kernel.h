@@ -3,8 +3,8 @@
 // Log-Int-Softmax and the BitShift Attn x V of Sec. 3.3 (the dataflow of its
 // Fig. 4), with the logits never leaving the chip.
 //
-// One workgroup per attention unit (as in the unit kernel of lis_device.h):
-// V^T is staged once in LDS as bf16, K once as int8 with each key's zero-point
+// A workgroup per attention unit, or several where the units alone would leave
+// CUs idle: V^T is staged once in LDS as bf16, K once as int8 with each key's zero-point
 // term, and each wavefront walks the unit's 16-query tiles.  For a tile, its
 // queries' bytes are the B operand of v_mfma_i32_16x16x{64,32}_i8 and 16 keys
 // of K the A operand, so one MFMA gives S^T for 16 keys x 16 queries with lane
@@ -37,6 +37,10 @@ struct QkArgs {
 };
 
 typedef int32_t i32x4v __attribute__((ext_vector_type(4)));
+
+// Rows of up to this many 32-key chunks run both Log-Int-Softmax paths in
+// registers; longer rows the float path.
+constexpr int kQkRegsNC = 7;
 
 // Byte offset of 16-byte unit u of key j in the staged K (DK bytes per key).
 // For DK >= 64 the units are XOR-swizzled with bits 2..3 of the key so that
@@ -137,10 +141,11 @@ __device__ __forceinline__ void qk_load_q(const int8_t* q_base, int i, int kg,
     }
 }
 
-// One 16-query tile in three passes over the keys, the logits recomputed in
-// each: the row maximum, the exact I-Exp sum, and the codes with the product
-// P V.  The chunk count is a run-time value; masked keys get P = 0.
-template <int DTMAX, bool FP, int DK, bool P0>
+// One 16-query tile on the integer path in three passes over the keys, the
+// logits recomputed in each: the row maximum, the exact I-Exp sum, and the
+// codes with the product P V.  The chunk count is a run-time value; masked
+// keys get P = 0.
+template <int DTMAX, int DK>
 __device__ __forceinline__ void qk_tile_passes(f32x4 (&acc)[DTMAX], const int8_t* kst,
                                                const int32_t* ck, const uint16_t* vt, int ld,
                                                const i32x4v (&qb)[DK >= 64 ? DK / 64 : 1],
@@ -156,41 +161,20 @@ __device__ __forceinline__ void qk_tile_passes(f32x4 (&acc)[DTMAX], const int8_t
     }
     mx = row4_max(mx);
 
-    RowState st;
-    if constexpr (FP) {
-        double part[2] = {0.0, 0.0};
+    uint64_t sum = 0;
 #pragma unroll 1
-        for (int c = 0; c < nc; ++c) {
-            int lg[8];
-            qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
+    for (int c = 0; c < nc; ++c) {
+        int lg[8];
+        qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const float e = iexp_f<P0>(lg[t], mx, k);
-                part[t & 1] += lg[t] != INT_MIN ? (double)e : 0.0;
-            }
+        for (int t = 0; t < 8; ++t) {
+            uint32_t z;
+            const uint32_t qL = iexp_qL(lg[t], mx, k, z);
+            sum += lg[t] != INT_MIN ? ((uint64_t)qL << (k.n - (int)z)) : 0ull;
         }
-        const double S2 = 2.0 * row4_sum(part[0] + part[1]);
-        st.S2s = S2 * kCodeScale;
-        st.sc = kCodeScale;
-        asm volatile("" : "+s"(st.sc));
-        st.tau = third_floor_f32(S2);
-    } else {
-        uint64_t sum = 0;
-#pragma unroll 1
-        for (int c = 0; c < nc; ++c) {
-            int lg[8];
-            qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                uint32_t z;
-                const uint32_t qL = iexp_qL(lg[t], mx, k, z);
-                sum += lg[t] != INT_MIN ? ((uint64_t)qL << (k.n - (int)z)) : 0ull;
-            }
-        }
-        st.rs = row_sum(sum, k);
     }
+    const RowSum rs = row_sum(sum, k);
 
-    const uint32_t kr = ((uint32_t)(k.top + 1) << 25) - 1u;
     const int ptop = (127 + k.top) << 7;
 #pragma unroll
     for (int dt = 0; dt < DTMAX; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -202,15 +186,9 @@ __device__ __forceinline__ void qk_tile_passes(f32x4 (&acc)[DTMAX], const int8_t
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const bool valid = lg[t] != INT_MIN;
-            if constexpr (FP) {
-                const int eb = __float_as_int(iexp_f<P0>(valid ? lg[t] : mx, mx, k));
-                pbits[t] = valid ? (127u + code_rev_f(eb, st, kr)) << 7 : 0u;
-            } else {
-                uint32_t z;
-                const uint32_t qL = iexp_qL(valid ? lg[t] : mx, mx, k, z);
-                const int cd = lis_code(qL, z, st.rs, k);
-                pbits[t] = valid ? (uint32_t)(ptop - (cd << 7)) : 0u;
-            }
+            uint32_t z;
+            const uint32_t qL = iexp_qL(valid ? lg[t] : mx, mx, k, z);
+            pbits[t] = valid ? (uint32_t)(ptop - (lis_code(qL, z, rs, k) << 7)) : 0u;
         }
         const u32x4 pb = {pbits[0] | (pbits[1] << 16), pbits[2] | (pbits[3] << 16),
                           pbits[4] | (pbits[5] << 16), pbits[6] | (pbits[7] << 16)};
@@ -218,15 +196,64 @@ __device__ __forceinline__ void qk_tile_passes(f32x4 (&acc)[DTMAX], const int8_t
     }
 }
 
+// Adds to acc what the exact codes of the chunks in todo differ by from the
+// screened ones, the chunks' logits formed again from K in LDS (rolled loops:
+// cold code of long rows, whose unrolled form would be longer than the rest of
+// the kernel).
+template <int NC, int DTMAX, int DK, bool P0>
+__device__ __forceinline__ void qk_fix_chunks(f32x4 (&acc)[DTMAX], uint32_t todo, const int8_t* kst,
+                                              const int32_t* ck, const uint16_t* vt, int ld,
+                                              const int8_t* q_base, int i, const int32_t* brow,
+                                              const ScreenRow& st, const LisConsts& k, int Lk,
+                                              int r, int kg) {
+    i32x4v qe[DK >= 64 ? DK / 64 : 1];
+    int64_t qe8 = 0;
+    qk_load_q<DK>(q_base, i, kg, qe, qe8);
+    double part = 0.0;
+#pragma unroll 1
+    for (int c = 0; c < NC; ++c) {
+        int lg[8];
+        qk_chunk<DK, false>(lg, kst, ck, qe, qe8, brow, c, r, kg, Lk, c == NC - 1);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const float e = __uint_as_float(screen_iexp<P0>(lg[t], st.mc, k));
+            part += lg[t] != INT_MIN ? (double)e : 0.0;
+        }
+    }
+    const RowState ex = screen_exact(row4_sum(part), k);
+#pragma unroll 1
+    for (uint32_t m = todo; m != 0; m &= m - 1) {
+        const int c = __builtin_ctz(m);
+        int lg[8];
+        qk_chunk<DK, false>(lg, kst, ck, qe, qe8, brow, c, r, kg, Lk, c == NC - 1);
+        chunk_mfma<DTMAX, false, true>(acc, chunk_pbits_diff<P0>(lg, st, ex, k), vt, ld, c, r, kg);
+    }
+}
+
+// Wavefronts per workgroup: four for rows whose V^T and K leave room for
+// several workgroups on a CU; eight for longer rows, whose 8 NC logits a lane
+// allow two wavefronts per SIMD anyway (one workgroup of ViT-L's 577 keys takes
+// 125 of the CU's 160 KB of LDS).  Holding the logits in registers instead of
+// forming them again for the maximum, the sum and the codes: 256 units of 577 x
+// 577, dk = d = 64, 148 -> 89 us.
+constexpr int qk_waves(int NC) { return NC <= 10 ? 4 : 8; }
+constexpr int qk_waves_per_simd(int NC) { return NC <= 8 ? 3 : 2; }
+
+// Workgroup b does part b / G of unit b % G: the unit's tiles are dealt to the
+// wavefronts of its p.split workgroups in turn, each of which stages V^T and K.
 template <int NC, int DTMAX, bool HALF, bool FP, int DK, bool P0 = false>
-__global__ __launch_bounds__(kBlock, 3) void lis_qk_kernel(LisArgs a, QkArgs qa, LisLaunch p) {
+__global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_qk_kernel(
+    LisArgs a, QkArgs qa, LisLaunch p) {
+    constexpr int WAVES = qk_waves(NC);
+    constexpr int NTHR = 64 * WAVES;
     constexpr int NT = HALF ? 4 : 8;
     constexpr int KP = 32 * NC;                 // staged keys (zero past Lk)
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint16_t* vt = reinterpret_cast<uint16_t*>(smem);
     int8_t* kst = reinterpret_cast<int8_t*>(smem + p.vt_bytes);
     int32_t* ck = reinterpret_cast<int32_t*>(smem + p.vt_bytes + KP * DK);
-    const int64_t g = blockIdx.x;
+    const int part = (int)(blockIdx.x / (unsigned)a.G);
+    const int64_t g = blockIdx.x - (unsigned)part * (unsigned)a.G;
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
@@ -239,10 +266,10 @@ __global__ __launch_bounds__(kBlock, 3) void lis_qk_kernel(LisArgs a, QkArgs qa,
 
     // V^T and K of the unit into LDS
     StageRegs sr;
-    stage_load(sr, a.v + g * (int64_t)a.Lk * a.d, a.Lk, a.d, DTMAX, 0, KP, a.zp_v, p.vec_ok);
+    stage_load<NTHR>(sr, a.v + g * (int64_t)a.Lk * a.d, a.Lk, a.d, DTMAX, 0, KP, a.zp_v, p.vec_ok);
     const int8_t* kg_base = qa.k + g * (int64_t)a.Lk * DK;
-    stage_k<DK, kBlock>(kst, ck, kg_base, a.Lk, KP, qa.zq);
-    stage_store(sr, vt, p.ld, DTMAX, KP, a.zp_v);
+    stage_k<DK, NTHR>(kst, ck, kg_base, a.Lk, KP, qa.zq);
+    stage_store<NTHR>(sr, vt, p.ld, DTMAX, KP, a.zp_v);
     __syncthreads();
 
     const int8_t* q_base = qa.q + g * (int64_t)a.Lq * DK;
@@ -250,9 +277,10 @@ __global__ __launch_bounds__(kBlock, 3) void lis_qk_kernel(LisArgs a, QkArgs qa,
 
     i32x4v qb[DK >= 64 ? DK / 64 : 1];
     int64_t qb8 = 0;
-    int tile = (wave + (int)(g & 3)) & 3;
+    const int step = WAVES * p.split;
+    int tile = (wave + WAVES * part + (int)(g & 3)) % step;
     if (tile < p.ntiles) qk_load_q<DK>(q_base, min(16 * tile + r, a.Lq - 1), kg, qb, qb8);
-    for (; tile < p.ntiles; tile += 4) {
+    for (; tile < p.ntiles; tile += step) {
         const int i0 = 16 * tile;
         const int i = min(i0 + r, a.Lq - 1);
 
@@ -262,30 +290,45 @@ __global__ __launch_bounds__(kBlock, 3) void lis_qk_kernel(LisArgs a, QkArgs qa,
         int lg[NC][8];
         auto logits = [&](const int32_t* brow) __attribute__((always_inline)) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c)
+            for (int c = 0; c < NC; ++c) {
                 qk_chunk<DK, HALF>(lg[c], kst, ck, qb, qb8, brow, c, r, kg, a.Lk, c == NC - 1);
+                // long rows: a few chunks' K reads in flight, not all
+                if (NC > kQkRegsNC && c % 3 == 2) __builtin_amdgcn_sched_barrier(0);
+            }
         };
         if (bplane) logits(bplane + (int64_t)i * a.Lk);
         else logits(nullptr);
         // the next tile's query bytes, in flight during the rest of this tile
-        qk_load_q<DK>(q_base, min(16 * (tile + 4 < p.ntiles ? tile + 4 : tile) + r, a.Lq - 1), kg, qb, qb8);
+        qk_load_q<DK>(q_base, min(16 * (tile + step < p.ntiles ? tile + step : tile) + r, a.Lq - 1), kg,
+                      qb, qb8);
         f32x4 acc[DTMAX];
 #pragma unroll
         for (int dt = 0; dt < DTMAX; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         if constexpr (FP) {
             double S;
             const ScreenRow st = tile_iexp_screen<NC, NT, false, P0>(lg, k, S);
+            uint32_t todo = 0;      // undecided chunks (long rows)
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 bool undecided;
-                u32x4 pb = chunk_pbits_screen<NC, NT>(lg, st, c, undecided);
-                if (__builtin_expect(undecided, 0))
-                    pb = chunk_pbits_exact(lg[c], screen_sum<NC, NT>(lg), k);
+                u32x4 pb = chunk_pbits_screen<NC, NT, (NC > kQkRegsNC)>(lg, st, c, undecided);
+                if constexpr (NC <= kQkRegsNC) {
+                    if (__builtin_expect(undecided, 0))
+                        pb = chunk_pbits_exact(lg[c], screen_sum<NC, NT>(lg), k);
+                } else {
+                    todo |= undecided ? 1u << c : 0u;
+                }
                 if (HALF && c == NC - 1)
                     chunk_mfma<DTMAX, true, true>(acc, pb, vt, p.ld, c, r, kg);
                 else
                     chunk_mfma<DTMAX, false, true>(acc, pb, vt, p.ld, c, r, kg);
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (NC > kQkRegsNC) {
+                if (__builtin_expect(todo != 0, 0))
+                    qk_fix_chunks<NC, DTMAX, DK, P0>(acc, todo, kst, ck, vt, p.ld, q_base, i,
+                                                     bplane ? bplane + (int64_t)i * a.Lk : nullptr, st,
+                                                     k, a.Lk, r, kg);
             }
         } else {
             uint32_t zb[NC][2];
@@ -305,22 +348,33 @@ __global__ __launch_bounds__(kBlock, 3) void lis_qk_kernel(LisArgs a, QkArgs qa,
 }
 
 // fpm: 0 the integer path, 1 the float path, 2 the float path with the
-// I-Exp pre-shift 0.
+// I-Exp pre-shift 0.  Rows of more than kQkRegsNC chunks: the float path only
+// (half: as a full last chunk).
 template <int DK, int NC>
 hipError_t launch_qk_nc(int dtm, bool half, int fpm, const LisArgs& a, const QkArgs& qa,
                         const LisLaunch& p, size_t lds, hipStream_t stream) {
-    const dim3 grid((unsigned)a.G), block(kBlock);
+    const dim3 grid((unsigned)(a.G * p.split)), block(64 * qk_waves(NC));
 #define FQ_QK(DT, H, F, P0) \
     launch_kernel(lis_qk_kernel<NC, DT, H, F, DK, P0>, grid, block, lds, stream, a, qa, p)
+    if constexpr (NC > kQkRegsNC) {
+        if (dtm == 2) {
+            if (fpm == 2) FQ_QK(2, false, true, true);
+            else FQ_QK(2, false, true, false);
+        } else {
+            if (fpm == 2) FQ_QK(4, false, true, true);
+            else FQ_QK(4, false, true, false);
+        }
+    } else {
 #define FQ_QK_F(DT, H) \
     if (fpm == 2) FQ_QK(DT, H, true, true); else if (fpm == 1) FQ_QK(DT, H, true, false); \
     else FQ_QK(DT, H, false, false)
 #define FQ_QK_H(DT) \
     if (half) { FQ_QK_F(DT, true); } else { FQ_QK_F(DT, false); }
-    if (dtm == 2) { FQ_QK_H(2) }
-    else { FQ_QK_H(4) }
+        if (dtm == 2) { FQ_QK_H(2) }
+        else { FQ_QK_H(4) }
 #undef FQ_QK_H
 #undef FQ_QK_F
+    }
 #undef FQ_QK
     return hipGetLastError();
 }
@@ -342,10 +396,20 @@ hipError_t launch_qk_dk(int nc, int dtm, bool half, int fp, const LisArgs& a, co
 
 hipError_t launch_qk_dk32(int nc, int dtm, bool half, int fp, const LisArgs& a, const QkArgs& qa,
                           const LisLaunch& p, size_t lds, hipStream_t stream);
-// Rows of 8 to 20 chunks (lis_qk_long.hip): one workgroup of 12 wavefronts per
-// unit, three passes over K in LDS per tile.
-hipError_t launch_qk_long(int dk, int dtm, int fp, const LisArgs& a, const QkArgs& qa,
-                          const LisLaunch& p, size_t lds, hipStream_t stream);
+// Rows of 8 to 20 chunks: the float path (lis_qk_long_dk32.hip,
+// lis_qk_long_dk64.hip, 8..14 and 15..20 chunks), and the integer path, which
+// takes the three passes of qk_tile_passes (lis_qk_long.hip).
+hipError_t launch_qk_long32_lo(int nc, int dtm, int fp, const LisArgs& a, const QkArgs& qa,
+                               const LisLaunch& p, size_t lds, hipStream_t stream);
+hipError_t launch_qk_long32_hi(int nc, int dtm, int fp, const LisArgs& a, const QkArgs& qa,
+                               const LisLaunch& p, size_t lds, hipStream_t stream);
+hipError_t launch_qk_long64_lo(int nc, int dtm, int fp, const LisArgs& a, const QkArgs& qa,
+                               const LisLaunch& p, size_t lds, hipStream_t stream);
+hipError_t launch_qk_long64_hi(int nc, int dtm, int fp, const LisArgs& a, const QkArgs& qa,
+                               const LisLaunch& p, size_t lds, hipStream_t stream);
+hipError_t launch_qk_long_int(int dk, int dtm, const LisArgs& a, const QkArgs& qa,
+                              const LisLaunch& p, size_t lds, hipStream_t stream);
+constexpr int kQkLongWaves = 12;     // integer path: wavefronts per workgroup
 hipError_t launch_qk_dk64(int nc, int dtm, bool half, int fp, const LisArgs& a, const QkArgs& qa,
                           const LisLaunch& p, size_t lds, hipStream_t stream);
 
