@@ -1,7 +1,9 @@
-// Log-Int-Softmax attention for gfx950: launch selection, the long-row
-// streaming kernel and the standalone BitShift Attn x V kernel.  The register
+// Log-Int-Softmax attention for gfx950: launch selection, the
+// streaming kernel for the longest rows and the standalone BitShift Attn x V kernel.  The register
 // kernels (lis_device.h) are instantiated per chunk count in lis_inst_*.hip.
-#include "lis_long.h"
+#include <algorithm>
+
+#include "lis_device.h"
 
 namespace fqvit {
 namespace lis {
@@ -334,7 +336,7 @@ constexpr size_t kMaxLdsBytes = 160 * 1024;
 // several tiles.  Measured on Swin-S (6144 units of 49 x 49, d = 32): two
 // wavefronts per unit 41.4 us, one 43.7 us, four 46.6-47.3 us.
 int unit_waves(int nc, int tiles16) {
-    if (nc > 4 || tiles16 > 4) return 4;
+    if (nc > 4 || tiles16 > 4) return lis::unit_long_waves(nc);
     return tiles16 == 1 ? 1 : 2;
 }
 
@@ -361,16 +363,20 @@ hipError_t launch_lis(const LisArgs& a, hipStream_t stream) {
     const size_t unit_lds = fused ? (size_t)unit_lds_dwords(dt) * sizeof(int32_t) : 0;
     p.n_logits = a.G * (int64_t)a.Lq * a.Lk;
     p.n_bias = a.bias ? (int64_t)a.Hb * a.Lq * a.Lk : 0;
-    p.tab_bytes = 0;
+    p.split = 1;
     p.codes_ldw = 0;
     const int64_t blocks = a.G * (int64_t)p.ntiles;
     const dim3 grid((unsigned)blocks);
     const bool fp = a.k.fp_ok != 0;
-    // Unit kernel: rows of up to 224 keys on the float path, V^T in one stage,
-    // and enough units to give every SIMD two busy wavefronts.
+    // Unit kernel: the fused product of rows of up to 640 keys on the float
+    // path, d <= 64, no codes output; codes only for rows of up to 224 keys and
+    // enough units to give every SIMD two busy wavefronts.
     const int tiles16 = (a.Lq + 15) / 16;
-    const bool unit_ok = nc <= kUnitMaxNC && fp && (!fused || (a.codes == nullptr && dt <= 4)) &&
-                         a.G <= 0x7FFFFFFF && a.G * std::min(4, tiles16) >= 2048;
+    const bool half = a.Lk - 32 * (nc - 1) <= 16;
+    const bool unit_ok =
+        fp && a.G <= 0x7FFFFFFF && (int64_t)a.Lq * a.Lk < ((int64_t)1 << 29) &&
+        (fused ? nc <= kUnitMaxNC && a.codes == nullptr && dt <= 4
+               : nc <= kUnitCodesMaxNC && a.G * std::min(4, tiles16) >= 2048);
     if (unit_ok) {
         LisLaunch u = p;
         u.ntiles = tiles16;
@@ -386,31 +392,26 @@ hipError_t launch_lis(const LisArgs& a, hipStream_t stream) {
             u.codes_ldw = (16 * row_bytes + 8 + 15) / 16 * 16;
             lds += (size_t)wpu * u.codes_ldw;
         }
-        const bool half = a.Lk - 32 * (nc - 1) <= 16;
-        return launch_lis_unit(nc, fused, dt, half, wpu, a, u, lds, stream);
+        // Workgroups per unit: a fused unit is dealt to as many as fill the
+        // workgroup slots of 256 CUs, at most one tile a wavefront (each stages
+        // V^T; see launch_lis_qk).  Measured against a workgroup per unit: 6
+        // units of 577 x 577, d = 48, 85 -> 24 us; 30 of them with a bias 122
+        // -> 36 us; 90 units of 325 x 325 with a bias 47 -> 26 us.
+        const int64_t slots =
+            256 * std::max<int64_t>(1, std::min<int64_t>(12 / wpu, kMaxLdsBytes / std::max<size_t>(lds, 1)));
+        const int64_t most = fused ? (tiles16 + wpu - 1) / wpu : 1;
+        u.split = (int)std::max<int64_t>(1, std::min<int64_t>(most, slots / a.G));
+        // One tile a wavefront: the tile kernel, whose rows stay in place (12
+        // units of 116 x 116 with a bias 6.2 us, 7.2 us in the unit kernel; 96
+        // units of 256 x 256 13.5 and 14.1 us).
+        const bool single = fused && u.split == most && nc <= kRegsFusedMaxNC && slots >= a.G;
+        if (!single && nc > kUnitCodesMaxNC)
+            return nc <= 14 ? launch_lis_unit_lo(nc, dt, a, u, lds, stream)
+                            : launch_lis_unit_hi(nc, dt, a, u, lds, stream);
+        if (!single) return launch_lis_unit(nc, fused, dt, half, wpu, a, u, lds, stream);
     }
-    // Long-row kernel: fused rows of 10 to 20 chunks on the float path, d <= 64,
-    // no codes output, when its I-Exp table (u_max + 1 entries, byte offsets in
-    // 16 bits) and V^T fit the LDS of one workgroup.
-    const bool long_ok = fused && fp && a.codes == nullptr && dt <= 4 && nc >= kLongMinNC &&
-                         nc <= kLongMaxNC && a.G <= 0x7FFFFFFF && a.k.u_max <= 16383 &&
-                         (int64_t)a.Lq * a.Lk * 4 < ((int64_t)1 << 31);
-    if (long_ok) {
-        LisLaunch l = p;
-        l.ntiles = tiles16;
-        l.kb = nc * 32;
-        l.ld = l.kb + 8;
-        l.vt_bytes = l.dpad * l.ld * (int)sizeof(uint16_t);
-        l.tab_bytes = (int)((((int64_t)a.k.u_max + 1) * 4 + 15) / 16 * 16);
-        const size_t lds = (size_t)l.tab_bytes + (size_t)l.vt_bytes;
-        if (lds <= kMaxLdsBytes) {
-            const bool half = a.Lk - 32 * (nc - 1) <= 16;
-            return nc <= 14 ? launch_lis_long_lo(nc, dt, half, a, l, lds, stream)
-                            : launch_lis_long_hi(nc, dt, half, a, l, lds, stream);
-        }
-    }
-    // Tile kernels: codes only for rows of up to 640 keys, the fused product
-    // (without a codes output, d <= 64) for rows of up to 288 keys.
+    // Tile kernels: codes only for rows of up to 640 keys, the fused product on
+    // the integer path (without a codes output, d <= 64) for rows of up to 288.
     const bool regs = fused ? (nc <= kRegsFusedMaxNC && a.codes == nullptr && dt <= 4) : nc <= 20;
     if (regs) {
         const size_t lds = (size_t)p.vt_bytes + out_lds;

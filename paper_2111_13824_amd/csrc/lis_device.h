@@ -238,10 +238,7 @@ __device__ __forceinline__ void load_full(int (&dst)[8], const int32_t* row, con
 // readable elements inside their tensors, so the chunk is read with full
 // vectors and masked afterwards.  HALF: only the first four keys (the last
 // chunk holds at most 16 keys).
-// DEFER: keys past Lk read with full vectors are left as loaded, to be masked
-// by mask_last when the chunk is used; masking them here would make the
-// wavefront wait for the load (and every load before it) right away.
-template <bool HALF, bool DEFER = false>
+template <bool HALF>
 __device__ __forceinline__ void load_chunk(int (&dst)[8], const int32_t* row, const int32_t* brow,
                                            int c, int kg, int Lk, bool vec_ok) {
     const int k0 = 32 * c + 4 * kg;
@@ -254,11 +251,9 @@ __device__ __forceinline__ void load_chunk(int (&dst)[8], const int32_t* row, co
                 const i32x4a4 ba = *reinterpret_cast<const i32x4a4*>(brow + k0);
                 dst[0] += ba.x; dst[1] += ba.y; dst[2] += ba.z; dst[3] += ba.w;
             }
-            if (!DEFER) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    if (k0 + t >= Lk) dst[t] = INT_MIN;
-            }
+            for (int t = 0; t < 4; ++t)
+                if (k0 + t >= Lk) dst[t] = INT_MIN;
         } else {
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -270,12 +265,10 @@ __device__ __forceinline__ void load_chunk(int (&dst)[8], const int32_t* row, co
     }
     if (vec_ok || k1 + 4 <= Lk) {
         load_full(dst, row, brow, c, kg);
-        if (!DEFER) {
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int key = (t < 4 ? k0 : k1 - 4) + t;
-                if (key >= Lk) dst[t] = INT_MIN;
-            }
+        for (int t = 0; t < 8; ++t) {
+            const int key = (t < 4 ? k0 : k1 - 4) + t;
+            if (key >= Lk) dst[t] = INT_MIN;
         }
     } else {
 #pragma unroll
@@ -299,8 +292,7 @@ __device__ __forceinline__ uint32_t last_valid(int kg, int Lk) {
     return m;
 }
 
-// The masking deferred by load_chunk<HALF, true>: keys past Lk of the last
-// chunk become INT_MIN.
+// Keys past Lk of the last chunk become INT_MIN.
 template <int NC, int NT>
 __device__ __forceinline__ void mask_last(int (&lg)[NC][8], uint32_t valid) {
 #pragma unroll
@@ -354,8 +346,7 @@ struct LisLaunch {
     int out_vec;    // output rows written through LDS as 16-byte units (d % 4 == 0, aligned out)
     int64_t n_logits;  // elements of the logits tensor (G Lq Lk)
     int64_t n_bias;    // elements of the bias tensor (Hb Lq Lk), 0 without bias
-    int tab_bytes;     // long-row kernel: LDS bytes of the I-Exp table (multiple of 16)
-    int split;         // workgroups per unit (unit, long-row and Q K kernels)
+    int split;         // workgroups per unit (unit and Q K kernels)
     int codes_ldw;     // unit kernel, codes only: LDS bytes per wavefront of the tile's
                        // code rows (dense rows, ld_codes = row bytes), 0: direct stores
 };
@@ -1050,62 +1041,100 @@ __device__ __forceinline__ RowPtrs row_ptrs(const LisArgs& a, const LisLaunch& p
     return rp;
 }
 
-// Row pointers inside one unit from its base offsets (unit kernel): the unit's
-// logit and bias planes are computed once, rows are offsets into them.
-struct UnitBase {
-    int64_t loff;   // offset of the unit's logits
-    int64_t boff;   // offset of its head's bias plane (0 without bias)
+// A unit's logits and its head's bias plane [Lq, Lk] (unit kernel), as buffer
+// descriptors: a load that is not needed (no next tile) gets an offset past the
+// plane and returns 0 without a memory access, and so do the dwords past the
+// plane's end in the last row's last chunk, so every load is unconditional.
+struct UnitPlanes {
+    __amdgpu_buffer_rsrc_t lg, bs;
+    bool bias;
 };
 
-template <int NC>
-__device__ __forceinline__ RowPtrs unit_row(const LisArgs& a, const LisLaunch& p, const UnitBase& ub,
-                                            int i) {
-    RowPtrs rp;
-    const int64_t roff = ub.loff + (int64_t)i * a.Lk;
-    rp.row = a.logits + roff;
-    const int64_t boff = ub.boff + (int64_t)i * a.Lk;
-    rp.brow = a.bias ? a.bias + boff : nullptr;
-    rp.tail_vec = roff + 32 * NC <= p.n_logits && (!rp.brow || boff + 32 * NC <= p.n_bias);
-    return rp;
+__device__ __forceinline__ UnitPlanes unit_planes(const LisArgs& a, int64_t g) {
+    const int64_t n = a.Lq * (int64_t)a.Lk;
+    const int bytes = (int)(4 * n);        // < 2^31 (checked by the launcher)
+    UnitPlanes up;
+    up.bias = a.bias != nullptr;
+    up.lg = __builtin_amdgcn_make_buffer_rsrc((void*)(a.logits + g * n), (short)0, bytes, 0x00020000);
+    up.bs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.bias ? a.bias + (g % a.Hb) * n : a.logits),
+                                              (short)0, up.bias ? bytes : 0, 0x00020000);
+    return up;
 }
 
-// Loads chunks [C0, C1) of a lane's keys.
-template <int NC, bool HALF, int C0 = 0, int C1 = NC, bool DEFER = false>
-__device__ __forceinline__ void tile_load(int (&lg)[NC][8], const RowPtrs& rp, int kg, int Lk) {
+// Byte offset of lane (row i, kg)'s first key; a negative row: nothing.
+__device__ __forceinline__ int unit_off(int i, int Lk, int kg) {
+    return i < 0 ? INT_MIN : 4 * (i * Lk + 4 * kg);
+}
+
+// Chunk c of a lane's keys, from the plane b at the lane's offset: keys past
+// Lk hold arbitrary values (masked when the tile is used: masked at the load,
+// they made the wavefront wait for the whole next tile at once).
+template <bool HALF>
+__device__ __forceinline__ void unit_load(int (&dst)[8], __amdgpu_buffer_rsrc_t b, int off, int c) {
+    const i32x4a4 x = __builtin_bit_cast(i32x4a4, __builtin_amdgcn_raw_buffer_load_b128(b, off + 128 * c, 0, 0));
+    dst[0] = x.x; dst[1] = x.y; dst[2] = x.z; dst[3] = x.w;
+    if (HALF) return;
+    const i32x4a4 y = __builtin_bit_cast(i32x4a4, __builtin_amdgcn_raw_buffer_load_b128(b, off + 128 * c + 64, 0, 0));
+    dst[4] = y.x; dst[5] = y.y; dst[6] = y.z; dst[7] = y.w;
+}
+
+// Chunks [C0, C1) of a lane's keys.
+template <int NC, bool HALF, int C0, int C1>
+__device__ __forceinline__ void unit_load_range(int (&lg)[NC][8], const UnitPlanes& up, int off) {
 #pragma unroll
     for (int c = C0; c < C1; ++c) {
-        if (c < NC - 1) load_full(lg[c], rp.row, rp.brow, c, kg);
-        else load_chunk<HALF, DEFER>(lg[NC - 1], rp.row, rp.brow, NC - 1, kg, Lk, rp.tail_vec);
+        if (HALF && c == NC - 1) unit_load<true>(lg[c], up.lg, off, c);
+        else unit_load<false>(lg[c], up.lg, off, c);
     }
 }
 
+// Adds the bias to a tile's logits and masks the keys past Lk.  The bias is
+// read when the tile is used (from L2: a head's plane serves many units), so
+// that the logits of the next tile need not be waited for when requested.
+template <int NC, bool HALF>
+__device__ __forceinline__ void unit_begin(int (&lg)[NC][8], const UnitPlanes& up, int off,
+                                           uint32_t valid) {
+    if (up.bias) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            int b[8];
+            if (HALF && c == NC - 1) unit_load<true>(b, up.bs, off, c);
+            else unit_load<false>(b, up.bs, off, c);
+#pragma unroll
+            for (int t = 0; t < (HALF && c == NC - 1 ? 4 : 8); ++t) lg[c][t] += b[t];
+        }
+    }
+    constexpr int NT = HALF ? 4 : 8;
+    mask_last<NC, NT>(lg, valid);
+#pragma unroll
+    for (int t = NT; t < 8; ++t) lg[NC - 1][t] = INT_MIN;
+}
+
 // ---------------------------------------------------------------------------
-// Unit kernel: one workgroup per attention unit, V^T staged once (single
-// stage), each wavefront walks the unit's 16-row tiles w', w' + 4, ... and
-// prefetches its next tile's logits while it computes the current one.  The
-// wave with the extra tiles rotates with the unit so that the SIMDs of a CU
-// share the remainder.  Float path only.  HALF: the last chunk holds at most
-// 16 keys and is contracted by the 16x16x16 MFMA.
+// Unit kernel: a workgroup per attention unit (several where the units alone
+// would leave CUs idle), V^T staged once (single stage), each wavefront walks
+// the unit's 16-row tiles and prefetches its next tile's logits while it
+// computes the current one.  The wave with the extra tiles rotates with the
+// unit so that the SIMDs of a CU share the remainder.  Float path only.  HALF:
+// the last chunk holds at most 16 keys and is contracted by the 16x16x16 MFMA.
+// Buffer loads (none for a missing next tile, none a byte past the plane)
+// against conditional global loads, and the bias added when the tile is used
+// instead of when it is requested: Swin-S (6144 x 49 x 49, d = 32, bias) 28.9
+// -> 24.2 us, ViT-B/16 41.0 -> 39.3 us.
 // ---------------------------------------------------------------------------
 // Prefetch of the next tile: its first PF chunks are requested right after
 // the I-Exp pass of the current tile, and chunk PF + c right after chunk c of
 // the current tile has gone through its MFMA (its registers are free by then),
 // so the next tile is in flight without holding two tiles in registers.
-// Fused rows of five or more chunks defer the masking of the last chunk's keys
-// past Lk to the chunk's use (mask_last): applied at the load, it made the
-// wavefront wait for the whole next tile right after requesting its last
-// chunk, before the current tile's output was stored.  The small-unit kernels
-// keep the masking at the load: deferred, they spilled at their register bound.
-constexpr bool unit_defer(int NC, bool FUSED) { return FUSED && NC >= 5; }
+constexpr int kUnitTwoBufNC = 7;     // rows whose tiles alternate between two buffers
+// Output of rows of 15 chunks and more by transposed blocks straight from the
+// registers (as the Q K kernel): the row-wise stores through LDS made them
+// spill (256 units of 577 x 577: 127.5 us with, 117.8 us without); up to 14
+// chunks the whole-row stores are the better ones (300 units of 400 x 400: 86.0
+// against 89.4 us).
+constexpr bool unit_transposed(int NC) { return NC >= 15; }
 constexpr int unit_prefetch(int NC, bool FUSED, int DTMAX, bool HALF) {
-    return unit_defer(NC, FUSED) && !(NC == 7 && DTMAX == 4 && !HALF) ? 2 : 0;
-}
-
-template <int NC, bool HALF, bool DEFER = false>
-__device__ __forceinline__ void load_one_chunk(int (&lg)[NC][8], const RowPtrs& rp, int c, int kg,
-                                               int Lk) {
-    if (c < NC - 1) load_full(lg[c], rp.row, rp.brow, c, kg);
-    else load_chunk<HALF, DEFER>(lg[NC - 1], rp.row, rp.brow, NC - 1, kg, Lk, rp.tail_vec);
+    return FUSED && NC >= 5 && NC <= kUnitTwoBufNC && !(NC == 7 && DTMAX == 4 && !HALF) ? 2 : 0;
 }
 
 // Maximum and sum over all 64 lanes: the four rows of sixteen lanes by the
@@ -1150,14 +1179,15 @@ __device__ __forceinline__ double wave_sum(double v) {
 // maximum, its exact sum and each key's code do not depend on the lane layout.
 template <int NC, int DTMAX>
 __device__ __forceinline__ void unit_row1(const LisArgs& a, const LisLaunch& p, const LisConsts& k,
-                                          const uint16_t* vt, int32_t* ot, const UnitBase& ub,
+                                          const uint16_t* vt, int32_t* ot, const UnitPlanes& up,
                                           int64_t g, int i0, int lane, int r, int kg) {
     static_assert(NC <= 2, "one key per lane");
     const int j = lane;
     const bool key = j < a.Lk && j < 32 * NC;
-    const int64_t off = (int64_t)i0 * a.Lk + j;
-    int v = INT_MIN;
-    if (key) v = a.logits[ub.loff + off] + (a.bias ? a.bias[ub.boff + off] : 0);
+    const int off = 4 * (i0 * a.Lk + j);
+    int v = (int)__builtin_amdgcn_raw_buffer_load_b32(up.lg, key ? off : INT_MIN, 0, 0);
+    if (up.bias) v += (int)__builtin_amdgcn_raw_buffer_load_b32(up.bs, key ? off : INT_MIN, 0, 0);
+    v = key ? v : INT_MIN;
     const int mx = wave_max(v);
     const float e = key ? iexp_f(v, mx, k) : 0.0f;
     const double S2 = 2.0 * wave_sum((double)e);
@@ -1185,25 +1215,27 @@ __device__ __forceinline__ void unit_row1(const LisArgs& a, const LisLaunch& p, 
     else store_out<DTMAX>(acc, a, g, i0, r, kg);
 }
 
-template <int NC, bool FUSED, int DTMAX, bool HALF, int WPU>
+template <int NC, bool FUSED, int DTMAX, bool HALF>
 __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], const LisArgs& a,
                                           const LisLaunch& p, const LisConsts& k, const uint16_t* vt,
-                                          int32_t* ot, const UnitBase& ub, int64_t g, int tile,
-                                          int ntl, int lane, int r, int kg, uint32_t valid) {
+                                          int32_t* ot, const UnitPlanes& up, int64_t g, int tile,
+                                          int step, int ntl, int lane, int r, int kg,
+                                          uint32_t valid) {
     constexpr int NT = HALF ? 4 : 8;
     constexpr int PF = unit_prefetch(NC, FUSED, DTMAX, HALF);
-    constexpr bool DF = unit_defer(NC, FUSED);
+    constexpr bool TR = unit_transposed(NC);
     const int i0 = 16 * tile;
-    // Always prefetch (a conditional load would keep the stale buffer live
-    // across the loop); past the last tile the current rows, still in cache,
-    // are read again.
-    const int nt = tile + WPU < ntl ? tile + WPU : tile;
-    const RowPtrs rn = unit_row<NC>(a, p, ub, min(16 * nt + r, a.Lq - 1));
-    if (DF) mask_last<NC, NT>(cur, valid);
+    unit_begin<NC, HALF>(cur, up, unit_off(min(i0 + r, a.Lq - 1), a.Lk, kg), valid);
+    const int nt = tile + step;
+    const int noff = unit_off(nt < ntl ? min(16 * nt + r, a.Lq - 1) : -1, a.Lk, kg);
+    auto next_chunk = [&](int c) __attribute__((always_inline)) {
+        if (HALF && c == NC - 1) unit_load<true>(nxt[c], up.lg, noff, c);
+        else unit_load<false>(nxt[c], up.lg, noff, c);
+    };
     if constexpr (FUSED) {
         double S;
         const ScreenRow st = tile_iexp_screen<NC, NT, true>(cur, k, S);
-        tile_load<NC, HALF, 0, PF, DF>(nxt, rn, kg, a.Lk);
+        unit_load_range<NC, HALF, 0, PF>(nxt, up, noff);
         uint32_t* scr = reinterpret_cast<uint32_t*>(ot);
         *reinterpret_cast<double*>(scr + 512 + 2 * lane) = S;
         f32x4 acc[DTMAX];
@@ -1215,21 +1247,21 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
             u32x4 pb = chunk_pbits_screen<NC, NT, true>(cur, st, c, undecided);
             if (__builtin_expect(undecided, 0)) pb = chunk_pbits_exact_lds(cur[c], k, scr, lane);
             if (HALF && c == NC - 1)
-                chunk_mfma<DTMAX, true>(acc, pb, vt, p.ld, c, r, kg);
+                chunk_mfma<DTMAX, true, TR>(acc, pb, vt, p.ld, c, r, kg);
             else
-                chunk_mfma<DTMAX, false>(acc, pb, vt, p.ld, c, r, kg);
-            if (PF + c < NC) load_one_chunk<NC, HALF, DF>(nxt, rn, PF + c, kg, a.Lk);
+                chunk_mfma<DTMAX, false, TR>(acc, pb, vt, p.ld, c, r, kg);
+            if (PF + c < NC) next_chunk(PF + c);
             // keep each chunk's V^T reads next to its MFMAs (hoisting them all
             // would take 4 DTMAX registers per chunk)
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (p.out_vec) store_out_rows<DTMAX>(acc, ot, a, g, i0, lane, r, kg);
+        if (TR) store_out_t<DTMAX>(acc, a, g, i0, r, kg, p.out_vec);
+        else if (p.out_vec) store_out_rows<DTMAX>(acc, ot, a, g, i0, lane, r, kg);
         else store_out<DTMAX>(acc, a, g, i0, r, kg);
         return;
     }
     uint32_t zb[NC][2];
     const RowState st = tile_iexp<NC, true, NT>(cur, zb, k);
-    tile_load<NC, HALF, 0, PF, DF>(nxt, rn, kg, a.Lk);
     if (p.codes_ldw != 0) {
         // Dense code rows: the tile's rows are one contiguous span of the codes
         // tensor.  They are gathered in LDS at the span's offset from a dword
@@ -1246,7 +1278,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
             int code[8];
             chunk_codes<NC, true, NT>(code, cur, zb, st, k, c);
             if (i < a.Lq) store_codes_row(cl + mis + r * nbr, a.Lk, k.top, c, kg, code);
-            if (PF + c < NC) load_one_chunk<NC, HALF, DF>(nxt, rn, PF + c, kg, a.Lk);
+            if (PF + c < NC) next_chunk(PF + c);
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_wave_barrier();
@@ -1270,7 +1302,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
             int code[8];
             chunk_codes<NC, true, NT>(code, cur, zb, st, k, c);
             if (i < a.Lq) store_codes_row(crow, a.Lk, k.top, c, kg, code);
-            if (PF + c < NC) load_one_chunk<NC, HALF, DF>(nxt, rn, PF + c, kg, a.Lk);
+            if (PF + c < NC) next_chunk(PF + c);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -1284,8 +1316,10 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
 // d <= 32 (96 registers: with the one-row tile path they spilled at 80; on
 // the Swin-S shapes five and six measured the same without it), and four
 // otherwise (128 registers).
+// Rows of more than 8 chunks hold more logits than three wavefronts per SIMD
+// leave registers for: two.
 constexpr int unit_waves_per_simd(int NC, bool FUSED, int DTMAX, int WPU) {
-    return WPU == 4 ? 3 : (FUSED && NC <= 2 && DTMAX <= 2 ? 5 : (!FUSED && NC <= 1) ? 6 : 4);
+    return NC > 8 ? 2 : WPU == 4 ? 3 : (FUSED && NC <= 2 && DTMAX <= 2 ? 5 : (!FUSED && NC <= 1) ? 6 : 4);
 }
 
 // WPU wavefronts per unit (4, or fewer for units of few tiles, so that each
@@ -1295,7 +1329,8 @@ __global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, WPU
     LisArgs a, LisLaunch p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint16_t* vt = reinterpret_cast<uint16_t*>(smem);
-    const int64_t g = blockIdx.x;
+    const int part = (int)(blockIdx.x / (unsigned)a.G);
+    const int64_t g = blockIdx.x - (unsigned)part * (unsigned)a.G;
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
@@ -1311,20 +1346,18 @@ __global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, WPU
         stage_load<64 * WPU>(sr, a.v + g * (int64_t)a.Lk * a.d, a.Lk, a.d, DTMAX, 0, 32 * NC, a.zp_v,
                              p.vec_ok);
 
-    UnitBase ub;
-    ub.loff = g * a.Lq * (int64_t)a.Lk;
-    ub.boff = a.bias ? (g % a.Hb) * a.Lq * (int64_t)a.Lk : 0;
+    const UnitPlanes up = unit_planes(a, g);
     // Fused rows of at most two chunks: a last tile of one row (units of
     // 16 m + 1 rows) is left out of the tile loop and taken by unit_row1 after
     // it, where neither tile buffer is live.
     constexpr bool kRow1 = FUSED && NC <= 2;
     const int ntl = kRow1 && (a.Lq & 15) == 1 ? p.ntiles - 1 : p.ntiles;
     int bufA[NC][8], bufB[NC][8];
-    int tile = (wave + (int)(g % WPU)) % WPU;
-    if (tile < ntl)
-        tile_load<NC, HALF, 0, NC, unit_defer(NC, FUSED)>(
-            bufA, unit_row<NC>(a, p, ub, min(16 * tile + r, a.Lq - 1)), kg, a.Lk);
-    const uint32_t valid = unit_defer(NC, FUSED) ? last_valid<NC>(kg, a.Lk) : 0xFFu;
+    const int step = WPU * p.split;
+    int tile = (wave + WPU * part + (int)(g % WPU)) % step;
+    unit_load_range<NC, HALF, 0, NC>(
+        bufA, up, unit_off(tile < ntl ? min(16 * tile + r, a.Lq - 1) : -1, a.Lk, kg));
+    const uint32_t valid = last_valid<NC>(kg, a.Lk);
     if constexpr (FUSED) {
         stage_store<64 * WPU>(sr, vt, p.ld, DTMAX, 32 * NC, a.zp_v);
         __syncthreads();
@@ -1332,18 +1365,27 @@ __global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, WPU
     // LDS per wavefront: the output transpose (fused) or the tile's code rows
     int32_t* ot = FUSED ? reinterpret_cast<int32_t*>(smem + p.vt_bytes) + wave * unit_lds_dwords(DTMAX)
                         : reinterpret_cast<int32_t*>(smem + wave * p.codes_ldw);
+    // Rows of more than seven chunks load each chunk of the next tile into the
+    // registers of the one just consumed: one body of code (two of 577 keys
+    // outgrow the instruction cache: 142.5 against 128.0 us on 256 units).
+    if constexpr (NC > kUnitTwoBufNC) {
+        for (; tile < ntl; tile += step)
+            unit_tile<NC, FUSED, DTMAX, HALF>(bufA, bufA, a, p, k, vt, ot, up, g, tile, step, ntl, lane, r,
+                                              kg, valid);
+        return;
+    }
     while (tile < ntl) {
-        unit_tile<NC, FUSED, DTMAX, HALF, WPU>(bufA, bufB, a, p, k, vt, ot, ub, g, tile, ntl, lane, r,
-                                               kg, valid);
-        tile += WPU;
+        unit_tile<NC, FUSED, DTMAX, HALF>(bufA, bufB, a, p, k, vt, ot, up, g, tile, step, ntl, lane, r,
+                                          kg, valid);
+        tile += step;
         if (tile >= ntl) break;
-        unit_tile<NC, FUSED, DTMAX, HALF, WPU>(bufB, bufA, a, p, k, vt, ot, ub, g, tile, ntl, lane, r,
-                                               kg, valid);
-        tile += WPU;
+        unit_tile<NC, FUSED, DTMAX, HALF>(bufB, bufA, a, p, k, vt, ot, up, g, tile, step, ntl, lane, r,
+                                          kg, valid);
+        tile += step;
     }
     if constexpr (kRow1) {
-        if (tile == ntl && ntl < p.ntiles)
-            unit_row1<NC, DTMAX>(a, p, k, vt, ot, ub, g, 16 * tile, lane, r, kg);
+        if (tile == ntl && ntl < p.ntiles)     // its tiles are part, part + step, ...
+            unit_row1<NC, DTMAX>(a, p, k, vt, ot, up, g, 16 * tile, lane, r, kg);
     }
 }
 
@@ -1385,7 +1427,14 @@ __global__ __launch_bounds__(kBlock, lis_waves_per_simd(NC)) void lis_kernel(Lis
     if (FUSED) stage_load(sr, vg, Lk, a.d, p.ncg, 0, min(p.kb, NC * 32), a.zp_v, p.vec_ok);
 
     int lg[NC][8];
-    tile_load<NC, false>(lg, row_ptrs<NC>(a, p, g, i), kg, Lk);
+    {
+        const RowPtrs rp = row_ptrs<NC>(a, p, g, i);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (c < NC - 1) load_full(lg[c], rp.row, rp.brow, c, kg);
+            else load_chunk<false>(lg[NC - 1], rp.row, rp.brow, NC - 1, kg, Lk, rp.tail_vec);
+        }
+    }
 
     if (FUSED) stage_store(sr, vt, p.ld, p.ncg, min(p.kb, NC * 32), a.zp_v);
 
@@ -1471,15 +1520,23 @@ hipError_t launch_lis_nc(bool fused, int dtm, bool fp, const LisArgs& a, const L
 }
 
 // Launch of the unit kernel for exactly NC chunks (NC <= kUnitMaxNC).
-constexpr int kUnitMaxNC = 7;
+constexpr int kUnitMaxNC = 20;          // fused
+constexpr int kUnitCodesMaxNC = 7;      // codes only
+// Wavefronts per workgroup of rows of more than four chunks: up to 10 chunks
+// several workgroups share a CU's LDS, beyond one takes it (V^T of 577 keys and
+// d = 64: 79 KB).
+constexpr int unit_long_waves(int NC) { return NC <= 10 ? 4 : 8; }
 
 template <int NC, int WPU>
 hipError_t launch_unit_nc_w(bool fused, int dtm, bool half, const LisArgs& a, const LisLaunch& p,
                             size_t lds, hipStream_t s) {
-#define FQ_UNIT(FUSED, DTM, HALF)                                                                  \
-    launch_kernel(lis_unit_kernel<NC, FUSED, DTM, HALF, WPU>, dim3((unsigned)a.G), dim3(64 * WPU), \
-                  lds, s, a, p)
-    if (!fused) {
+#define FQ_UNIT(FUSED, DTM, HALF)                                                       \
+    launch_kernel(lis_unit_kernel<NC, FUSED, DTM, HALF, WPU>, dim3((unsigned)(a.G * p.split)), \
+                  dim3(64 * WPU), lds, s, a, p)
+    if constexpr (NC > kUnitCodesMaxNC) {       // fused; half as a full last chunk
+        if (dtm == 2) FQ_UNIT(true, 2, false);
+        else FQ_UNIT(true, 4, false);
+    } else if (!fused) {
         if (half) FQ_UNIT(false, 1, true);
         else FQ_UNIT(false, 1, false);
     } else if (dtm == 2) {
@@ -1501,7 +1558,7 @@ hipError_t launch_unit_nc(bool fused, int dtm, bool half, int wpu, const LisArgs
         if (wpu == 1) return launch_unit_nc_w<NC, 1>(fused, dtm, half, a, p, lds, s);
         if (wpu == 2) return launch_unit_nc_w<NC, 2>(fused, dtm, half, a, p, lds, s);
     }
-    return launch_unit_nc_w<NC, 4>(fused, dtm, half, a, p, lds, s);
+    return launch_unit_nc_w<NC, unit_long_waves(NC)>(fused, dtm, half, a, p, lds, s);
 }
 
 // Per chunk-count launchers, instantiated in lis_inst_lo.hip (1..10 chunks),
@@ -1512,6 +1569,11 @@ hipError_t launch_lis_regs_hi(int nc, bool fused, int dtm, bool fp, const LisArg
                               const LisLaunch& p, dim3 grid, size_t lds, hipStream_t stream);
 hipError_t launch_lis_unit(int nc, bool fused, int dtm, bool half, int wpu, const LisArgs& a,
                            const LisLaunch& p, size_t lds, hipStream_t stream);
+// Fused rows of 8..20 chunks (lis_unit_long.hip, in two halves).
+hipError_t launch_lis_unit_lo(int nc, int dtm, const LisArgs& a, const LisLaunch& p, size_t lds,
+                              hipStream_t stream);
+hipError_t launch_lis_unit_hi(int nc, int dtm, const LisArgs& a, const LisLaunch& p, size_t lds,
+                              hipStream_t stream);
 
 }  // namespace lis
 }  // namespace fqvit

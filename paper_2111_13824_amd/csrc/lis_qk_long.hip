@@ -8,13 +8,42 @@
 // registers, and its logits cost two MFMAs per 32-key chunk from LDS, so each
 // 16-query tile takes the three passes of qk_tile_passes.  The chunk count is a
 // run-time value; the last chunk's keys past Lk get P = 0.
-#include "lis_long.h"
 #include "lis_qk_kernel.h"
 
 namespace fqvit {
 namespace lis {
 
 constexpr int kQkLongBlock = 64 * kQkLongWaves;
+
+// V^T of a whole unit (keys [0, kp), kp a multiple of 32) staged by a workgroup
+// of NTHREADS threads, as stage_store does: item = (16-column group, key quad).
+template <int DTMAX, int NTHREADS>
+__device__ __forceinline__ void long_stage_vt(uint16_t* vt, int ld, const int8_t* vg, int Lk, int d,
+                                              int kp, int zp, bool vec_ok) {
+    const int nquads = kp / 4;
+    const float off = (float)(128 + zp);
+    for (int idx = threadIdx.x; idx < nquads * DTMAX; idx += NTHREADS) {
+        const int cg = idx / nquads;
+        const int jj = 4 * (idx - cg * nquads);
+        const int dd = 16 * cg;
+        u32x4 w[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            w[t] = (dd < d && jj + t < Lk) ? load_v16(vg + (int64_t)(jj + t) * d, dd, d, vec_ok)
+                                           : u32x4{0u, 0u, 0u, 0u};
+        const int pos = (jj & ~31) + chunk_pos(jj & 31);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) w[t] ^= 0x80808080u;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            float f[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) f[t] = (float)((w[t][q >> 2] >> (8 * (q & 3))) & 0xFFu) - off;
+            *reinterpret_cast<u32x2*>(vt + (16 * cg + q) * ld + pos) =
+                u32x2{bf16_pair(f[0], f[1]), bf16_pair(f[2], f[3])};
+        }
+    }
+}
 
 template <int DTMAX, int DK>
 __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, QkArgs qa,
