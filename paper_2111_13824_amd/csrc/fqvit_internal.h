@@ -120,6 +120,7 @@ struct AvMfma {
     int nks;              // kp / 64
     int ldv;              // LDS row stride of V^T in bytes (kp + 16)
     int ntiles;           // 16-row tiles per unit
+    int split;            // workgroups per unit
     int unit_bytes;       // code bytes a unit spans: (Lq - 1) ld_codes + ceil(Lk / 2)
     int vec_out;          // 16-byte output stores (d % 4 == 0, 16-byte aligned out)
     int vec_v;            // V rows read as 16-byte units (d % 16 == 0, 16-byte aligned V)

@@ -22,8 +22,8 @@
 // cannot express: a unit holding one is computed again afterwards, exactly,
 // on the vector ALUs (from the V^T staged for it).
 //
-// One workgroup of four wavefronts per attention unit: V^T of the unit is
-// staged in LDS as int8 (keys padded to a multiple of 64 with zeros); each
+// A workgroup of four wavefronts per attention unit (several where the units
+// alone would leave CUs idle): V^T of the unit is staged in LDS as int8 (keys padded to a multiple of 64 with zeros); each
 // wavefront walks the unit's 16-row tiles.  Lane (r, kq) takes query row
 // i0 + r and keys 64 ks + 16 kq .. + 15 of each 64-key step, its code bytes
 // straight from memory as aligned dwords and funnel shifts:
@@ -31,14 +31,18 @@
 //     0,2,4,6 | 1,3,5,7 | 8,10,.. | 9,11,..; V^T is staged in the same key
 //     order), each P_k byte a table lookup (one or two byte permutes over
 //     8-entry tables chosen at compile time, and a select on the code's bit 3);
-//   * byte codes: sixteen bytes in key order; per key the 64-bit value
-//     2^(8 k + e) (s = 7 k + e) holds its P_k in byte k, and a 4 x 8 byte
-//     transpose of four keys gives the range dwords.
+//   * byte codes: sixteen bytes in key order, four keys a dword: k and 2^e
+//     (s = 7 k + e) of each as a byte, packed, and per range the bytes whose k
+//     it is, selected by one byte permute (25 instructions for four keys; a
+//     64-bit 2^(8 k + e) per key and a byte transpose took about 55).  With it
+//     and the joined sums (av_join64): ViT-B/16, 8-bit codes, 54 -> 35 us.
 // The B operand of the MFMA is P_k^T (keys x rows), the A operand V^T
 // (columns x keys), so the output lane (r, kq) holds columns 16 ct + 4 kq .. + 3
 // of row i0 + r.  The codes of the next four (nibble codes) or two (byte
 // codes) steps are in flight per wavefront across tile boundaries, and the
 // kernel is held to two wavefronts per SIMD (at most 256 registers).
+#include <algorithm>
+
 #include "fqvit_launch.h"
 #include "lis_device.h"
 
@@ -47,6 +51,8 @@ namespace lis {
 namespace {
 
 typedef int32_t av_i32x4 __attribute__((ext_vector_type(4)));
+typedef uint64_t av_u64x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
 
 // Arguments shared by both products.
 struct AvK {
@@ -170,6 +176,25 @@ struct AvRanges {
 template <bool BYTES>
 constexpr int av_win() { return BYTES ? 2 : 4; }
 
+// sum_k 2^(7 k) acc[k][t] mod 2^64.  Every sum is at most 128 64 kAvMfmaMaxLk =
+// 2^23 in magnitude, so neighbouring ranges join in 32 bits; one 64-bit
+// multiply-add joins each further pair (seven 64-bit shifts and adds took four
+// times the instructions).
+template <int NS>
+__device__ __forceinline__ uint64_t av_join64(const av_i32x4 (&acc)[NS], int t) {
+    static_assert(kAvMfmaMaxLk <= 1024 && NS <= 7, "pairs within 32 bits");
+    int32_t b[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < NS; k += 2)
+        b[k / 2] = acc[k][t] + (k + 1 < NS ? (int32_t)((uint32_t)acc[k + 1 < NS ? k + 1 : k][t] << 7) : 0);
+    int64_t v = b[0];
+    if (NS > 2) v += (int64_t)b[1] * (1 << 14);
+    if (NS > 4) v += (int64_t)b[2] * (1 << 28);
+    uint64_t u = (uint64_t)v;
+    if (NS > 6) u += (uint64_t)(uint32_t)(b[3] << 10) << 32;
+    return u;
+}
+
 // CB: code width (1..4 bits: nibbles; 5: bytes, W = 31; 8: bytes, W = 44);
 // ZS: the zero point is not 0 (sum_j P_j needed); WIDE: int64 output, with
 // the floor of codes above W.
@@ -182,7 +207,11 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
     constexpr int NW = BYTES ? 5 : 3;
     extern __shared__ __attribute__((aligned(16))) uint8_t vt[];   // [16 DT][ldv] int8
     __shared__ int s_floor;
-    const int64_t g = xcd_remap(blockIdx.x, a.G);
+    // part of unit g: tiles 4 part + wave, then every 4 m.split
+    const int64_t lb = xcd_remap(blockIdx.x, a.G * m.split);
+    const int64_t g = lb / m.split;
+    const int first = 4 * (int)(lb - g * m.split);
+    const int step = 4 * m.split;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int r = lane & 15;
@@ -199,15 +228,14 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
     const __amdgpu_buffer_rsrc_t cr = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(ubase - (uint64_t)mis), (short)0, (m.unit_bytes + mis + 3) & ~3, 0x00020000);
 
-    // The wavefront's steps: tiles wave, wave + 4, ..., each in nks steps of
-    // 64 keys; (pt, pks) is the step whose codes are requested next.  The first
+    // The wavefront's steps: its tiles, each in nks steps of 64 keys; (pt, pks) is the step whose codes are requested next.  The first
     // window is requested before V^T is staged.
-    const int my_tiles = m.ntiles > wave ? (m.ntiles - wave + 3) / 4 : 0;
+    const int my_tiles = m.ntiles > first + wave ? (m.ntiles - first - wave + step - 1) / step : 0;
     const int nsteps = my_tiles * nks;
     auto row_of = [&](int t) {
         return t < m.ntiles ? min(16 * t + r, a.Lq - 1) * a.ld_codes + mis : -1;
     };
-    int pt = wave, pks = 0;
+    int pt = first + wave, pks = 0;
     int prow = row_of(pt);
     uint32_t cb[kAvWin][NW];
 #pragma unroll
@@ -215,7 +243,7 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
         av_load_codes<BYTES>(cb[u], cr, prow, pks, kq);
         if (++pks == nks) {
             pks = 0;
-            pt += 4;
+            pt += step;
             prow = row_of(pt);
         }
     }
@@ -240,10 +268,12 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
     // nibble codes above W (b <= 3; the wide product only)
     const uint32_t over_mask = (uint32_t)(~a.W & 15) * 0x01010101u;
     bool floor_seen = false;
+    uint32_t floor_bits = 0;        // byte codes: bit 7 of a byte: a code above W
+    constexpr int kW = CB == 5 ? 31 : 44;
 
     av_i32x4 acc[DT][NS];
     uint32_t psum[NS];
-    int ks = 0, tile = wave;
+    int ks = 0, tile = first + wave;
     int rowoff = row_of(tile);
     for (int s0 = 0; s0 < nsteps; s0 += kAvWin) {
 #pragma unroll
@@ -275,7 +305,7 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
             av_load_codes<BYTES>(cb[u], cr, prow, pks, kq);
             if (++pks == nks) {
                 pks = 0;
-                pt += 4;
+                pt += step;
                 prow = row_of(pt);
             }
             const bool last = ks == nks - 1;
@@ -285,26 +315,28 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
                 const uint32_t kmask = last ? keep_last[q] : ~0u;
                 uint32_t pb[NS];
                 if constexpr (BYTES) {
-                    // per key: s = W - code; 2^(8 k + e) with s = 7 k + e holds
-                    // P_k in byte k (floor(37 s / 256) = floor(s / 7) for s <= 44)
-                    uint32_t xl[4], xh[4];
+                    // Four keys at a time, a byte each: s = W - code, kk =
+                    // floor(s / 7) = floor(37 s / 256) (s <= 44), and P_k =
+                    // 2^(s - 7 kk) where kk = k.  A code above W garbles its
+                    // dword; its outputs are computed again below.
+                    if (WIDE)
+                        floor_bits |= (((cw[q] & 0x7F7F7F7Fu) + (uint32_t)(127 - kW) * 0x01010101u) |
+                                       cw[q]) & kmask;
+                    const uint32_t s4 = (uint32_t)kW * 0x01010101u - cw[q];
+                    const u16x2_t se = __builtin_bit_cast(u16x2_t, s4 & 0x00FF00FFu) * (uint16_t)37;
+                    const u16x2_t so = __builtin_bit_cast(u16x2_t, (s4 >> 8) & 0x00FF00FFu) * (uint16_t)37;
+                    const uint32_t kk = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, so),
+                                                              __builtin_bit_cast(uint32_t, se), 0x07030501u);
+                    const uint32_t e4 = s4 - ((kk << 3) - kk);
+                    const uint32_t p4 = __builtin_amdgcn_perm(0x00402010u, 0x08040201u, e4 & 0x07070707u);
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const int c = (int)((cw[q] >> (8 * t)) & 0xFFu);
-                        const int sv = a.W - c;
-                        if (WIDE) floor_seen |= sv < 0 && ((kmask >> (8 * t)) & 1u);
-                        const int kk = (sv * 37) >> 8;
-                        const uint64_t x = sv >= 0 ? (uint64_t)1 << (sv + kk) : 0ull;
-                        xl[t] = (uint32_t)x;
-                        xh[t] = (uint32_t)(x >> 32);
+                    for (int k = 0; k < NS; ++k) {
+                        // 0xFF in the bytes with kk = k
+                        const uint32_t mk = __builtin_amdgcn_perm(k >= 4 ? 0xFFu << (8 * (k - 4)) : 0u,
+                                                                  k < 4 ? 0xFFu << (8 * k) : 0u,
+                                                                  kk & 0x07070707u);
+                        pb[k] = p4 & mk;
                     }
-                    uint32_t y[4];
-                    av_transpose4(y, xl[0], xl[1], xl[2], xl[3]);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) pb[k] = y[k];
-                    av_transpose4(y, xh[0], xh[1], xh[2], xh[3]);
-#pragma unroll
-                    for (int k = 4; k < NS; ++k) pb[k] = y[k - 4];
                 } else {
                     if (WIDE && R::N < 15) floor_seen |= (cw[q] & over_mask & kmask) != 0;
                     const uint32_t sel = cw[q] & 0x07070707u;
@@ -364,14 +396,20 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
                         int64_t* orow = reinterpret_cast<int64_t*>(a.out) + (g * a.Lq + row) * (int64_t)d;
 #pragma unroll
                         for (int ct = 0; ct < DT; ++ct) {
+                            uint64_t res[4];
 #pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                uint64_t v = 0;
+                            for (int t = 0; t < 4; ++t) res[t] = av_join64<NS>(acc[ct], t) - zterm;
+                            const int c0 = 16 * ct + 4 * kq;
+                            if (m.vec_out && c0 + 3 < d) {
+                                // streaming: the output is not read again here
+                                __builtin_nontemporal_store(av_u64x2{res[0], res[1]},
+                                                            reinterpret_cast<av_u64x2*>(orow + c0));
+                                __builtin_nontemporal_store(av_u64x2{res[2], res[3]},
+                                                            reinterpret_cast<av_u64x2*>(orow + c0 + 2));
+                            } else {
 #pragma unroll
-                                for (int k = 0; k < NS; ++k)
-                                    v += (uint64_t)(int64_t)acc[ct][k][t] << (7 * k);
-                                const int c = 16 * ct + 4 * kq + t;
-                                if (c < d) orow[c] = (int64_t)(v - zterm);
+                                for (int t = 0; t < 4; ++t)
+                                    if (c0 + t < d) orow[c0 + t] = (int64_t)res[t];
                             }
                         }
                     }
@@ -410,23 +448,28 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
                     }
                 }
                 ks = 0;
-                tile += 4;
+                tile += step;
                 rowoff = row_of(tile);
             }
         }
     }
 
     if constexpr (WIDE) {
-        // A code above W somewhere in the unit: every output of the unit again,
-        // term by term (V from the staged V^T, codes from memory).
+        // A code above W somewhere in the workgroup's tiles: all their outputs
+        // again, term by term (V from the staged V^T, codes from memory).
+        if (BYTES) floor_seen = (floor_bits & 0x80808080u) != 0;
         if (__ballot(floor_seen) != 0 && lane == 0) atomicOr(&s_floor, 1);
         __syncthreads();
         if (s_floor) {
             const uint8_t* cu = a.codes + g * a.Lq * (int64_t)a.ld_codes;
             int64_t* ou = reinterpret_cast<int64_t*>(a.out) + g * a.Lq * (int64_t)d;
-            for (int idx = threadIdx.x; idx < a.Lq * d; idx += 256) {
-                const int i = idx / d;
-                const int c = idx - i * d;
+            // rows of the workgroup's groups of four tiles, 64 rows each
+            const int groups = (m.ntiles - first + step - 1) / step;
+            for (int idx = threadIdx.x; idx < groups * 64 * d; idx += 256) {
+                const int q = idx / d;
+                const int c = idx - q * d;
+                const int i = 16 * (first + step * (q >> 6)) + (q & 63);
+                if (i >= a.Lq) continue;
                 const uint8_t* crow = cu + (int64_t)i * a.ld_codes;
                 uint64_t sum = 0;
                 for (int j = 0; j < Lk; ++j) {
@@ -444,7 +487,7 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
 
 template <int DT, int CB, bool WIDE>
 hipError_t launch_cfg(const AvK& a, const AvMfma& m, size_t lds, hipStream_t s) {
-    const dim3 grid((unsigned)a.G), block(256);
+    const dim3 grid((unsigned)(a.G * m.split)), block(256);
     if (a.zp_v != 0) launch_kernel(attn_v_mfma_kernel<DT, CB, true, WIDE>, grid, block, lds, s, a, m);
     else launch_kernel(attn_v_mfma_kernel<DT, CB, false, WIDE>, grid, block, lds, s, a, m);
     return hipGetLastError();
@@ -480,6 +523,11 @@ hipError_t launch_any(const AvK& a, int bits, bool wide, hipStream_t stream) {
     if (dt > 4 || a.Lk > kAvMfmaMaxLk || ub + 6 > 0x7FFFFFFF || a.G > 0x7FFFFFFF)
         return hipErrorNotSupported;
     m.unit_bytes = (int)ub;
+    // Workgroups per unit: as many as fill the slots of 256 CUs (two of four
+    // wavefronts a CU, by registers), at most one tile a wavefront; each stages
+    // V^T.  Measured (codes and product): 32 units of 389 x 389, 4-bit codes,
+    // 40.7 -> 19.6 us; 6 units of 145 x 145, 8-bit codes, 21.1 -> 13.0 us.
+    m.split = (int)std::max<int64_t>(1, std::min<int64_t>((m.ntiles + 3) / 4, 512 / a.G));
     // nibble codes: P_k byte tables, code c -> 2^(s - 7 k) for 7 k <= s < 7 k + 7,
     // s = W - c
     for (int k = 0; k < 3; ++k) {
