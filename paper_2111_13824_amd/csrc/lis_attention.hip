@@ -368,15 +368,16 @@ hipError_t launch_lis(const LisArgs& a, hipStream_t stream) {
     const int64_t blocks = a.G * (int64_t)p.ntiles;
     const dim3 grid((unsigned)blocks);
     const bool fp = a.k.fp_ok != 0;
-    // Unit kernel: the fused product of rows of up to 640 keys on the float
-    // path, d <= 64, no codes output; codes only for rows of up to 224 keys and
-    // enough units to give every SIMD two busy wavefronts.
+    // Unit kernel: rows of up to 640 keys on the float path; the fused product
+    // for d <= 64 and no codes output; codes only of more than 224 keys for
+    // dense code rows.
     const int tiles16 = (a.Lq + 15) / 16;
     const bool half = a.Lk - 32 * (nc - 1) <= 16;
-    const bool unit_ok =
-        fp && a.G <= 0x7FFFFFFF && (int64_t)a.Lq * a.Lk < ((int64_t)1 << 29) &&
-        (fused ? nc <= kUnitMaxNC && a.codes == nullptr && dt <= 4
-               : nc <= kUnitCodesMaxNC && a.G * std::min(4, tiles16) >= 2048);
+    const int row_bytes = a.k.top > 15 ? a.Lk : (a.Lk + 1) / 2;
+    const bool dense = !fused && a.ld_codes == row_bytes;
+    const bool unit_ok = fp && a.G <= 0x7FFFFFFF && (int64_t)a.Lq * a.Lk < ((int64_t)1 << 29) &&
+                         nc <= kUnitMaxNC &&
+                         (fused ? a.codes == nullptr && dt <= 4 : dense || nc <= kUnitShortNC);
     if (unit_ok) {
         LisLaunch u = p;
         u.ntiles = tiles16;
@@ -384,30 +385,29 @@ hipError_t launch_lis(const LisArgs& a, hipStream_t stream) {
         u.ld = u.kb + 8;
         u.vt_bytes = fused ? u.dpad * u.ld * (int)sizeof(uint16_t) : 0;
         const int wpu = unit_waves(nc, tiles16);
-        size_t lds = (size_t)u.vt_bytes + unit_lds * wpu;
+        size_t lds = (size_t)u.vt_bytes +
+                     (fused ? unit_lds : (size_t)kScreenLds * sizeof(int32_t)) * wpu;
         // codes only, dense rows: each wavefront gathers its tile's code rows
         // in LDS and writes them as one span
-        const int row_bytes = a.k.top > 15 ? a.Lk : (a.Lk + 1) / 2;
-        if (!fused && a.ld_codes == row_bytes) {
+        if (dense) {
             u.codes_ldw = (16 * row_bytes + 8 + 15) / 16 * 16;
             lds += (size_t)wpu * u.codes_ldw;
         }
-        // Workgroups per unit: a fused unit is dealt to as many as fill the
-        // workgroup slots of 256 CUs, at most one tile a wavefront (each stages
-        // V^T; see launch_lis_qk).  Measured against a workgroup per unit: 6
+        // Workgroups per unit: a unit is dealt to as many as fill the workgroup
+        // slots of 256 CUs, at most one tile a wavefront (each stages V^T; see launch_lis_qk).  Measured against a workgroup per unit: 6
         // units of 577 x 577, d = 48, 85 -> 24 us; 30 of them with a bias 122
         // -> 36 us; 90 units of 325 x 325 with a bias 47 -> 26 us.
         const int64_t slots =
             256 * std::max<int64_t>(1, std::min<int64_t>(12 / wpu, kMaxLdsBytes / std::max<size_t>(lds, 1)));
-        const int64_t most = fused ? (tiles16 + wpu - 1) / wpu : 1;
+        const int64_t most = (tiles16 + wpu - 1) / wpu;
         u.split = (int)std::max<int64_t>(1, std::min<int64_t>(most, slots / a.G));
         // One tile a wavefront: the tile kernel, whose rows stay in place (12
         // units of 116 x 116 with a bias 6.2 us, 7.2 us in the unit kernel; 96
         // units of 256 x 256 13.5 and 14.1 us).
-        const bool single = fused && u.split == most && nc <= kRegsFusedMaxNC && slots >= a.G;
-        if (!single && nc > kUnitCodesMaxNC)
-            return nc <= 14 ? launch_lis_unit_lo(nc, dt, a, u, lds, stream)
-                            : launch_lis_unit_hi(nc, dt, a, u, lds, stream);
+        const bool single = u.split == most && slots >= a.G && (!fused || nc <= kRegsFusedMaxNC);
+        if (!single && nc > kUnitShortNC)
+            return nc <= 14 ? launch_lis_unit_lo(nc, fused, dt, a, u, lds, stream)
+                            : launch_lis_unit_hi(nc, fused, dt, a, u, lds, stream);
         if (!single) return launch_lis_unit(nc, fused, dt, half, wpu, a, u, lds, stream);
     }
     // Tile kernels: codes only for rows of up to 640 keys, the fused product on

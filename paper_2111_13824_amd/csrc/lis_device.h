@@ -46,6 +46,9 @@
 // The host picks the float path whenever its exactness conditions hold.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "fqvit_launch.h"
 
 namespace fqvit {
@@ -60,6 +63,16 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>)
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+    static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
 
 // Block index -> logical tile so that the tiles of one unit run on one XCD
 // (blocks are dealt round-robin to the eight XCDs) and share its L2.
@@ -300,6 +313,7 @@ __device__ __forceinline__ void mask_last(int (&lg)[NC][8], uint32_t valid) {
 }
 
 // Store the 8 codes of lane (r, kg) in chunk c as nibbles (even key low).
+template <bool FULL = false>
 __device__ __forceinline__ void store_codes(uint8_t* crow, int nbytes, int c, int kg,
                                             const int (&code)[8]) {
     const int b0 = 16 * c + 2 * kg;
@@ -308,26 +322,28 @@ __device__ __forceinline__ void store_codes(uint8_t* crow, int nbytes, int c, in
     const uint8_t v1 = (uint8_t)(code[2] | (code[3] << 4));
     const uint8_t v2 = (uint8_t)(code[4] | (code[5] << 4));
     const uint8_t v3 = (uint8_t)(code[6] | (code[7] << 4));
-    if (b0 < nbytes) crow[b0] = v0;
-    if (b0 + 1 < nbytes) crow[b0 + 1] = v1;
-    if (b1 < nbytes) crow[b1] = v2;
-    if (b1 + 1 < nbytes) crow[b1 + 1] = v3;
+    if (FULL || b0 < nbytes) crow[b0] = v0;
+    if (FULL || b0 + 1 < nbytes) crow[b0 + 1] = v1;
+    if (FULL || b1 < nbytes) crow[b1] = v2;
+    if (FULL || b1 + 1 < nbytes) crow[b1 + 1] = v3;
 }
 
 // Store the 8 codes of lane (r, kg) in chunk c of a row: nibbles for codes of
 // up to 4 bits (top <= 15), else one byte per code (keys past Lk skipped).
+// FULL: every key of the chunk exists.
+template <bool FULL = false>
 __device__ __forceinline__ void store_codes_row(uint8_t* crow, int Lk, int top, int c, int kg,
                                                 const int (&code)[8]) {
     if (top > 15) {
         const int k0 = 32 * c + 4 * kg;
 #pragma unroll
         for (int t = 0; t < 4; ++t)
-            if (k0 + t < Lk) crow[k0 + t] = (uint8_t)code[t];
+            if (FULL || k0 + t < Lk) crow[k0 + t] = (uint8_t)code[t];
 #pragma unroll
         for (int t = 0; t < 4; ++t)
-            if (k0 + 16 + t < Lk) crow[k0 + 16 + t] = (uint8_t)code[4 + t];
+            if (FULL || k0 + 16 + t < Lk) crow[k0 + 16 + t] = (uint8_t)code[4 + t];
     } else {
-        store_codes(crow, (Lk + 1) >> 1, c, kg, code);
+        store_codes<FULL>(crow, (Lk + 1) >> 1, c, kg, code);
     }
 }
 
@@ -826,6 +842,45 @@ __device__ __forceinline__ u32x4 chunk_pbits_exact_lds(const int (&e)[8], const 
     return pb;
 }
 
+// Codes of chunk c from the screened values (masked keys of the last chunk, held
+// as 0, and the entries past NT get code 0); undecided as in chunk_pbits_screen.
+template <int NC, int NT>
+__device__ __forceinline__ void chunk_codes_screen(int (&code)[8], const int (&lg)[NC][8],
+                                                   const ScreenRow& st, const LisConsts& k, int c,
+                                                   bool& undecided) {
+    const int top = screen_top(k);
+    uint32_t chk = 0;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        if (c == NC - 1 && t >= NT) {
+            code[t] = 0;
+            continue;
+        }
+        uint32_t e = (uint32_t)lg[c][t];
+        asm volatile("" : "+v"(e));       // keeps the chunk's arithmetic in its place
+        const uint32_t b = screen_key(e, st);
+        chk = max(chk, b << 9);
+        const int cd = top - (int)(b >> 23);
+        code[t] = (c == NC - 1 && e == 0u) ? 0 : cd;
+    }
+    undecided = screen_failed(chk, st);
+}
+
+// The codes of an undecided chunk by the binary64 form, as chunk_pbits_exact_lds.
+__device__ __forceinline__ void chunk_codes_exact_lds(int (&code)[8], const int (&e)[8],
+                                                      const LisConsts& k, uint32_t* scr, int lane) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) scr[64 * t + lane] = (uint32_t)e[t];
+    const RowState ex = screen_exact(*reinterpret_cast<const double*>(scr + 512 + 2 * lane), k);
+#pragma unroll 1
+    for (int t = 0; t < 8; ++t) {
+        const int eb = (int)scr[64 * t + lane];
+        scr[64 * t + lane] = eb != 0 ? (uint32_t)code_f(eb + (k.n << 23), ex, k.top) : 0u;
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) code[t] = (int)scr[64 * t + lane];
+}
+
 // Codes of chunk c; in the last chunk masked keys (held as 0) get code 0 and
 // the entries past NT are 0.
 template <int NC, bool FP, int NT>
@@ -977,9 +1032,14 @@ __device__ __forceinline__ void store_out(const f32x4 (&acc)[DTMAX], const LisAr
 template <int DTMAX>
 constexpr int out_lds_dwords() { return 16 * (16 * DTMAX + 4); }
 
-// The unit kernel's LDS per wavefront: that block, or 640 dwords (an undecided
-// chunk's keys and the row sums) where it is smaller.
-constexpr int unit_lds_dwords(int dtm) { return 16 * (16 * dtm + 4) > 640 ? 16 * (16 * dtm + 4) : 640; }
+// LDS dwords of an undecided chunk's keys and the row sums (64 x 8 + 64 x 2).
+constexpr int kScreenLds = 640;
+
+// The fused unit kernel's LDS per wavefront: that block, or kScreenLds dwords
+// where it is smaller.
+constexpr int unit_lds_dwords(int dtm) {
+    return 16 * (16 * dtm + 4) > kScreenLds ? 16 * (16 * dtm + 4) : kScreenLds;
+}
 
 template <int DTMAX>
 __device__ __forceinline__ void store_out_rows(const f32x4 (&acc)[DTMAX], int32_t* ot,
@@ -1127,6 +1187,7 @@ __device__ __forceinline__ void unit_begin(int (&lg)[NC][8], const UnitPlanes& u
 // the current tile has gone through its MFMA (its registers are free by then),
 // so the next tile is in flight without holding two tiles in registers.
 constexpr int kUnitTwoBufNC = 7;     // rows whose tiles alternate between two buffers
+constexpr int kUnitShortNC = 7;      // rows instantiated with half last chunks (lis_inst_unit.hip)
 // Output of rows of 15 chunks and more by transposed blocks straight from the
 // registers (as the Q K kernel): the row-wise stores through LDS made them
 // spill (256 units of 577 x 577: 127.5 us with, 117.8 us without); up to 14
@@ -1260,27 +1321,39 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
         else store_out<DTMAX>(acc, a, g, i0, r, kg);
         return;
     }
-    uint32_t zb[NC][2];
-    const RowState st = tile_iexp<NC, true, NT>(cur, zb, k);
-    if (p.codes_ldw != 0) {
+    // Codes only (screened: ViT-B/16 50.2 -> 46.2 us with 8-bit codes; 60 units
+    // of 577 x 577 24 us less than in the tile kernel).  ot: the code rows'
+    // region, then an undecided chunk's.
+    double S;
+    const ScreenRow st = tile_iexp_screen<NC, NT, true>(cur, k, S);
+    uint32_t* scr = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(ot) + p.codes_ldw);
+    *reinterpret_cast<double*>(scr + 512 + 2 * lane) = S;
+    const int i = i0 + r;
+    auto codes_of = [&](int c, int (&code)[8]) __attribute__((always_inline)) {
+        bool undecided;
+        chunk_codes_screen<NC, NT>(code, cur, st, k, c, undecided);
+        if (__builtin_expect(undecided, 0)) chunk_codes_exact_lds(code, cur[c], k, scr, lane);
+    };
+    if (NC > kUnitShortNC || p.codes_ldw != 0) {    // (long rows: always dense)
         // Dense code rows: the tile's rows are one contiguous span of the codes
         // tensor.  They are gathered in LDS at the span's offset from a dword
-        // boundary (mis), then written as whole aligned dwords, the partial
-        // dwords at both ends byte by byte.
-        const int i = i0 + r;
+        // boundary (mis; a row past Lq is gathered but not written), then
+        // written as whole aligned dwords, the partial dwords at both ends byte
+        // by byte.
         const int nbr = k.top > 15 ? a.Lk : (a.Lk + 1) >> 1;
         const int rows = min(16, a.Lq - i0);
         uint8_t* cl = reinterpret_cast<uint8_t*>(ot);
         uint8_t* span = a.codes + (g * a.Lq + i0) * (int64_t)nbr;
         const int mis = (int)(reinterpret_cast<uintptr_t>(span) & 3);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
+        // (unrolled by the front end: the loop is too long for the unroller)
+        static_for<NC>([&](auto ci) __attribute__((always_inline)) {
+            constexpr int c = decltype(ci)::value;
             int code[8];
-            chunk_codes<NC, true, NT>(code, cur, zb, st, k, c);
-            if (i < a.Lq) store_codes_row(cl + mis + r * nbr, a.Lk, k.top, c, kg, code);
+            codes_of(c, code);
+            store_codes_row<(c < NC - 1)>(cl + mis + r * nbr, a.Lk, k.top, c, kg, code);
             if (PF + c < NC) next_chunk(PF + c);
             __builtin_amdgcn_sched_barrier(0);
-        }
+        });
         __builtin_amdgcn_wave_barrier();
         uint8_t* gb = span - mis;
         const int end = mis + rows * nbr;
@@ -1295,12 +1368,11 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
         }
         __builtin_amdgcn_wave_barrier();
     } else {
-        const int i = i0 + r;
         uint8_t* crow = a.codes + (g * a.Lq + min(i, a.Lq - 1)) * (int64_t)a.ld_codes;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             int code[8];
-            chunk_codes<NC, true, NT>(code, cur, zb, st, k, c);
+            codes_of(c, code);
             if (i < a.Lq) store_codes_row(crow, a.Lk, k.top, c, kg, code);
             if (PF + c < NC) next_chunk(PF + c);
             __builtin_amdgcn_sched_barrier(0);
@@ -1364,7 +1436,7 @@ __global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, WPU
     }
     // LDS per wavefront: the output transpose (fused) or the tile's code rows
     int32_t* ot = FUSED ? reinterpret_cast<int32_t*>(smem + p.vt_bytes) + wave * unit_lds_dwords(DTMAX)
-                        : reinterpret_cast<int32_t*>(smem + wave * p.codes_ldw);
+                        : reinterpret_cast<int32_t*>(smem + wave * (p.codes_ldw + 4 * kScreenLds));
     // Rows of more than seven chunks load each chunk of the next tile into the
     // registers of the one just consumed: one body of code (two of 577 keys
     // outgrow the instruction cache: 142.5 against 128.0 us on 256 units).
@@ -1520,8 +1592,7 @@ hipError_t launch_lis_nc(bool fused, int dtm, bool fp, const LisArgs& a, const L
 }
 
 // Launch of the unit kernel for exactly NC chunks (NC <= kUnitMaxNC).
-constexpr int kUnitMaxNC = 20;          // fused
-constexpr int kUnitCodesMaxNC = 7;      // codes only
+constexpr int kUnitMaxNC = 20;
 // Wavefronts per workgroup of rows of more than four chunks: up to 10 chunks
 // several workgroups share a CU's LDS, beyond one takes it (V^T of 577 keys and
 // d = 64: 79 KB).
@@ -1533,8 +1604,9 @@ hipError_t launch_unit_nc_w(bool fused, int dtm, bool half, const LisArgs& a, co
 #define FQ_UNIT(FUSED, DTM, HALF)                                                       \
     launch_kernel(lis_unit_kernel<NC, FUSED, DTM, HALF, WPU>, dim3((unsigned)(a.G * p.split)), \
                   dim3(64 * WPU), lds, s, a, p)
-    if constexpr (NC > kUnitCodesMaxNC) {       // fused; half as a full last chunk
-        if (dtm == 2) FQ_UNIT(true, 2, false);
+    if constexpr (NC > kUnitShortNC) {       // half as a full last chunk
+        if (!fused) FQ_UNIT(false, 1, false);
+        else if (dtm == 2) FQ_UNIT(true, 2, false);
         else FQ_UNIT(true, 4, false);
     } else if (!fused) {
         if (half) FQ_UNIT(false, 1, true);
@@ -1569,11 +1641,11 @@ hipError_t launch_lis_regs_hi(int nc, bool fused, int dtm, bool fp, const LisArg
                               const LisLaunch& p, dim3 grid, size_t lds, hipStream_t stream);
 hipError_t launch_lis_unit(int nc, bool fused, int dtm, bool half, int wpu, const LisArgs& a,
                            const LisLaunch& p, size_t lds, hipStream_t stream);
-// Fused rows of 8..20 chunks (lis_unit_long.hip, in two halves).
-hipError_t launch_lis_unit_lo(int nc, int dtm, const LisArgs& a, const LisLaunch& p, size_t lds,
-                              hipStream_t stream);
-hipError_t launch_lis_unit_hi(int nc, int dtm, const LisArgs& a, const LisLaunch& p, size_t lds,
-                              hipStream_t stream);
+// Rows of 8..20 chunks (lis_unit_long.hip, in two halves).
+hipError_t launch_lis_unit_lo(int nc, bool fused, int dtm, const LisArgs& a, const LisLaunch& p,
+                              size_t lds, hipStream_t stream);
+hipError_t launch_lis_unit_hi(int nc, bool fused, int dtm, const LisArgs& a, const LisLaunch& p,
+                              size_t lds, hipStream_t stream);
 
 }  // namespace lis
 }  // namespace fqvit

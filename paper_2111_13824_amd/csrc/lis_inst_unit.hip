@@ -4,7 +4,7 @@
 namespace fqvit {
 namespace lis {
 
-static_assert(kUnitCodesMaxNC == 7, "instantiated chunk counts");
+static_assert(kUnitShortNC == 7, "instantiated chunk counts");
 
 hipError_t launch_lis_unit(int nc, bool fused, int dtm, bool half, int wpu, const LisArgs& a,
                            const LisLaunch& p, size_t lds, hipStream_t stream) {
