@@ -183,7 +183,9 @@ def lis_softmax_log4(logits, s_logit: float, bits: int = 4, exp_n: int = 20, bia
     import torch
     G, Lq, Lk = logits.shape
     if codes is None:
-        codes = torch.zeros((G, Lq, codes_ld(Lk, bits)), dtype=torch.uint8, device=logits.device)
+        # rows without padding: the kernel writes every byte (an odd row's last
+        # high nibble 0)
+        codes = torch.empty((G, Lq, codes_ld(Lk, bits)), dtype=torch.uint8, device=logits.device)
     if codes.dim() != 3 or codes.shape[:2] != (G, Lq):
         raise ValueError("codes must be [G, Lq, ld_codes]")
     Hb = 0
