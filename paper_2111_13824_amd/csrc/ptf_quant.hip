@@ -358,6 +358,19 @@ __device__ __forceinline__ int requant_one(int32_t q, int64_t N2, int N1, int64_
     return (int)yc - half;
 }
 
+// The same for N1 >= 32 (every M below 1/2): the rounding term enters the 64-bit
+// multiply-add, the shift leaves the high word alone, and a value outside
+// [-2^31, 2^31) after zp cannot arise (|w| < 2^30 there).  Six instructions an
+// element instead of twenty: 768 x 197 x 64 elements, after the attention from Q and
+// K (both): 37.7 -> 36.8 us.
+__device__ __forceinline__ int requant_hi(int32_t q, int32_t N2, uint64_t half_ulp, int sh, int zp_c,
+                                          int lo, int hi) {
+    const int64_t prod = (int64_t)N2 * (int64_t)q + (int64_t)half_ulp;
+    const int w = (int)(prod >> 32) >> sh;
+    return min(max(w + zp_c, lo), hi);
+}
+
+template <bool HI>
 __global__ __launch_bounds__(kBlock) void requant_kernel(const int32_t* q, int64_t n, int64_t N2,
                                                          int N1, int zp_c, int bits, int vec4,
                                                          int8_t* y) {
@@ -366,6 +379,12 @@ __global__ __launch_bounds__(kBlock) void requant_kernel(const int32_t* q, int64
     const int64_t hi = (1 << bits) - 1;
     const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
+    auto one = [&](int32_t x) __attribute__((always_inline)) {
+        if constexpr (HI)
+            return requant_hi(x, (int32_t)N2, (uint64_t)1 << (N1 - 1), N1 - 32, zp_c, -half, half - 1);
+        else
+            return requant_one(x, N2, N1, zp, hi, half);
+    };
     if (vec4) {
         // four 16-byte loads in flight per thread before any is converted
         constexpr int kU = 4;
@@ -382,18 +401,18 @@ __global__ __launch_bounds__(kBlock) void requant_kernel(const int32_t* q, int64
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
                 const int64_t i = i0 + u * stride;
-                const uint32_t p = ((uint32_t)requant_one(v[u].x, N2, N1, zp, hi, half) & 0xFFu) |
-                                   (((uint32_t)requant_one(v[u].y, N2, N1, zp, hi, half) & 0xFFu) << 8) |
-                                   (((uint32_t)requant_one(v[u].z, N2, N1, zp, hi, half) & 0xFFu) << 16) |
-                                   ((uint32_t)requant_one(v[u].w, N2, N1, zp, hi, half) << 24);
+                const uint32_t p = ((uint32_t)one(v[u].x) & 0xFFu) |
+                                   (((uint32_t)one(v[u].y) & 0xFFu) << 8) |
+                                   (((uint32_t)one(v[u].z) & 0xFFu) << 16) |
+                                   ((uint32_t)one(v[u].w) << 24);
                 if (i < n4) __builtin_nontemporal_store(p, y4 + i);
             }
         }
         for (int64_t i = (n / 4) * 4 + tid; i < n; i += stride)
-            y[i] = (int8_t)requant_one(q[i], N2, N1, zp, hi, half);
+            y[i] = (int8_t)one(q[i]);
     } else {
         for (int64_t i = tid; i < n; i += stride)
-            y[i] = (int8_t)requant_one(q[i], N2, N1, zp, hi, half);
+            y[i] = (int8_t)one(q[i]);
     }
 }
 
@@ -463,8 +482,13 @@ hipError_t launch_requant(const RequantArgs& a, hipStream_t stream) {
                       (reinterpret_cast<uintptr_t>(a.y) & 3) == 0)
                          ? 1
                          : 0;
-    launch_kernel(requant_kernel, dim3(grid_for(a.n, kBlock * 16, 8192)), dim3(kBlock), 0, stream,
-                  a.q, a.n, a.N2, a.N1, a.zp, a.bits, vec4, a.y);
+    const dim3 grid(grid_for(a.n, kBlock * 16, 8192));
+    if (a.N1 >= 32)
+        launch_kernel(requant_kernel<true>, grid, dim3(kBlock), 0, stream, a.q, a.n, a.N2, a.N1, a.zp,
+                      a.bits, vec4, a.y);
+    else
+        launch_kernel(requant_kernel<false>, grid, dim3(kBlock), 0, stream, a.q, a.n, a.N2, a.N1, a.zp,
+                      a.bits, vec4, a.y);
     return hipGetLastError();
 }
 
