@@ -58,7 +58,7 @@ PAPER_CONTEXT = {
     "vit_b_gbitops_8_8_4_ptf_lis": 1117.76,
 }
 LIS_SOURCES = ["lis_device.h", "lis_attention.hip", "lis_inst_lo.hip", "lis_inst_hi.hip",
-               "lis_inst_unit.hip", "fqvit_internal.h", "fqvit_launch.h"]
+               "lis_inst_unit.hip", "lis_unit_long.hip", "fqvit_internal.h", "fqvit_launch.h"]
 
 
 def _code_only(text):
@@ -120,9 +120,7 @@ def recorded_traffic(workload):
 def _lis_fused(name):
     """Whether a Log-Int-Softmax kernel instance is the fused head (its FUSED
     template argument: second of lis_unit_kernel and lis_kernel, first of
-    lis_kernel_stream; the long-row kernel is fused only)."""
-    if "lis_long_kernel" in name:
-        return True
+    lis_kernel_stream)."""
     args = name.split("<", 1)[1].split(">", 1)[0].split(",")
     pos = 0 if "lis_kernel_stream" in name else 1
     return args[pos].strip() == "true"
