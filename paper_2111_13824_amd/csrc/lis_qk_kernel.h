@@ -76,17 +76,36 @@ __device__ __forceinline__ void stage_k(int8_t* kst, int32_t* ck, const int8_t* 
     }
 }
 
+// The bias of chunk c's logits in their layout (keys past Lk, which only the
+// last chunk holds: 0).
+__device__ __forceinline__ void qk_load_bias(i32x4v (&b)[2], const int32_t* brow, int c, int kg,
+                                             int Lk, bool last) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int j0 = 32 * c + 16 * h + 4 * kg;
+        if (!last) {
+            const i32x4a4 v = *reinterpret_cast<const i32x4a4*>(brow + j0);
+            b[h] = i32x4v{v.x, v.y, v.z, v.w};
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) b[h][t] = j0 + t < Lk ? brow[j0 + t] : 0;
+        }
+    }
+}
+
 // Logits of chunk c for lane (query r, group kg): keys 32 c + 4 kg + t
 // (t < 4) and 32 c + 16 + 4 kg + (t - 4), INT_MIN past Lk (only the last chunk
-// holds such keys); the bias row (if any) added.  The per-key zero-point
-// terms are the MFMA's initial accumulator (same layout: lane (r, kg) holds
-// keys j0 .. j0 + 3).  The per-query term zp_q zp_k dk - zp_k sum_c q[i][c] is
-// left out: the Log-Int-Softmax of a row depends only on the differences of
-// its logits.  HALF: the last chunk holds at most 16 keys.
-template <int DK, bool HALF>
+// holds such keys).  The per-key zero-point terms, with the bias b if there is
+// one, are the MFMA's initial accumulator (same layout: lane (r, kg) holds
+// keys j0 .. j0 + 3): the logits then stay in the four registers that the MFMA
+// writes, where adding the bias to them afterwards scattered them and made
+// rows of 13 chunks and more spill.  The per-query term zp_q zp_k dk - zp_k
+// sum_c q[i][c] is left out: the Log-Int-Softmax of a row depends only on the
+// differences of its logits.  HALF: the last chunk holds at most 16 keys.
+template <int DK, bool HALF, bool BIAS>
 __device__ __forceinline__ void qk_chunk(int (&lg)[8], const int8_t* kst, const int32_t* ck,
                                          const i32x4v (&qb)[DK >= 64 ? DK / 64 : 1], int64_t qb8,
-                                         const int32_t* brow, int c, int r, int kg, int Lk,
+                                         const i32x4v (&b)[2], int c, int r, int kg, int Lk,
                                          bool last) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -99,6 +118,7 @@ __device__ __forceinline__ void qk_chunk(int (&lg)[8], const int8_t* kst, const 
         const int key = 16 * kt + r;          // A operand row of this lane
         const int j0 = 16 * kt + 4 * kg;      // keys of s[0..3]
         i32x4v s = *reinterpret_cast<const i32x4v*>(ck + j0);
+        if (BIAS) s += b[h];
         if constexpr (DK >= 64) {
 #pragma unroll
             for (int m = 0; m < DK / 64; ++m) {
@@ -110,18 +130,11 @@ __device__ __forceinline__ void qk_chunk(int (&lg)[8], const int8_t* kst, const 
             s = __builtin_amdgcn_mfma_i32_16x16x32_i8(av, qb8, s, 0, 0, 0);
         }
         if (!last) {
-            if (brow) {
-                const i32x4a4 b = *reinterpret_cast<const i32x4a4*>(brow + j0);
-                s += i32x4v{b.x, b.y, b.z, b.w};
-            }
 #pragma unroll
             for (int t = 0; t < 4; ++t) lg[4 * h + t] = s[t];
         } else {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const bool ok = j0 + t < Lk;
-                lg[4 * h + t] = ok ? s[t] + (brow && ok ? brow[j0 + t] : 0) : INT_MIN;
-            }
+            for (int t = 0; t < 4; ++t) lg[4 * h + t] = j0 + t < Lk ? s[t] : INT_MIN;
         }
     }
 }
@@ -145,7 +158,7 @@ __device__ __forceinline__ void qk_load_q(const int8_t* q_base, int i, int kg,
 // logits recomputed in each: the row maximum, the exact I-Exp sum, and the
 // codes with the product P V.  The chunk count is a run-time value; masked
 // keys get P = 0.
-template <int DTMAX, int DK>
+template <int DTMAX, int DK, bool BIAS>
 __device__ __forceinline__ void qk_tile_passes(f32x4 (&acc)[DTMAX], const int8_t* kst,
                                                const int32_t* ck, const uint16_t* vt, int ld,
                                                const i32x4v (&qb)[DK >= 64 ? DK / 64 : 1],
@@ -155,7 +168,9 @@ __device__ __forceinline__ void qk_tile_passes(f32x4 (&acc)[DTMAX], const int8_t
 #pragma unroll 1
     for (int c = 0; c < nc; ++c) {
         int lg[8];
-        qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
+        i32x4v b[2];
+        if (BIAS) qk_load_bias(b, brow, c, kg, Lk, c == nc - 1);
+        qk_chunk<DK, false, BIAS>(lg, kst, ck, qb, qb8, b, c, r, kg, Lk, c == nc - 1);
 #pragma unroll
         for (int t = 0; t < 8; ++t) mx = max(mx, lg[t]);
     }
@@ -165,7 +180,9 @@ __device__ __forceinline__ void qk_tile_passes(f32x4 (&acc)[DTMAX], const int8_t
 #pragma unroll 1
     for (int c = 0; c < nc; ++c) {
         int lg[8];
-        qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
+        i32x4v b[2];
+        if (BIAS) qk_load_bias(b, brow, c, kg, Lk, c == nc - 1);
+        qk_chunk<DK, false, BIAS>(lg, kst, ck, qb, qb8, b, c, r, kg, Lk, c == nc - 1);
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             uint32_t z;
@@ -181,7 +198,9 @@ __device__ __forceinline__ void qk_tile_passes(f32x4 (&acc)[DTMAX], const int8_t
 #pragma unroll 1
     for (int c = 0; c < nc; ++c) {
         int lg[8];
-        qk_chunk<DK, false>(lg, kst, ck, qb, qb8, brow, c, r, kg, Lk, c == nc - 1);
+        i32x4v b[2];
+        if (BIAS) qk_load_bias(b, brow, c, kg, Lk, c == nc - 1);
+        qk_chunk<DK, false, BIAS>(lg, kst, ck, qb, qb8, b, c, r, kg, Lk, c == nc - 1);
         uint32_t pbits[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
@@ -200,7 +219,7 @@ __device__ __forceinline__ void qk_tile_passes(f32x4 (&acc)[DTMAX], const int8_t
 // screened ones, the chunks' logits formed again from K in LDS (rolled loops:
 // cold code of long rows, whose unrolled form would be longer than the rest of
 // the kernel).
-template <int NC, int DTMAX, int DK, bool P0>
+template <int NC, int DTMAX, int DK, bool P0, bool BIAS>
 __device__ __forceinline__ void qk_fix_chunks(f32x4 (&acc)[DTMAX], uint32_t todo, const int8_t* kst,
                                               const int32_t* ck, const uint16_t* vt, int ld,
                                               const int8_t* q_base, int i, const int32_t* brow,
@@ -213,7 +232,9 @@ __device__ __forceinline__ void qk_fix_chunks(f32x4 (&acc)[DTMAX], uint32_t todo
 #pragma unroll 1
     for (int c = 0; c < NC; ++c) {
         int lg[8];
-        qk_chunk<DK, false>(lg, kst, ck, qe, qe8, brow, c, r, kg, Lk, c == NC - 1);
+        i32x4v b[2];
+        if (BIAS) qk_load_bias(b, brow, c, kg, Lk, c == NC - 1);
+        qk_chunk<DK, false, BIAS>(lg, kst, ck, qe, qe8, b, c, r, kg, Lk, c == NC - 1);
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const float e = __uint_as_float(screen_iexp<P0>(lg[t], st.mc, k));
@@ -225,7 +246,9 @@ __device__ __forceinline__ void qk_fix_chunks(f32x4 (&acc)[DTMAX], uint32_t todo
     for (uint32_t m = todo; m != 0; m &= m - 1) {
         const int c = __builtin_ctz(m);
         int lg[8];
-        qk_chunk<DK, false>(lg, kst, ck, qe, qe8, brow, c, r, kg, Lk, c == NC - 1);
+        i32x4v b[2];
+        if (BIAS) qk_load_bias(b, brow, c, kg, Lk, c == NC - 1);
+        qk_chunk<DK, false, BIAS>(lg, kst, ck, qe, qe8, b, c, r, kg, Lk, c == NC - 1);
         chunk_mfma<DTMAX, false, true>(acc, chunk_pbits_diff<P0>(lg, st, ex, k), vt, ld, c, r, kg);
     }
 }
@@ -238,10 +261,16 @@ __device__ __forceinline__ void qk_fix_chunks(f32x4 (&acc)[DTMAX], uint32_t todo
 // 577, dk = d = 64, 148 -> 89 us.
 constexpr int qk_waves(int NC) { return NC <= 10 ? 4 : 8; }
 constexpr int qk_waves_per_simd(int NC) { return NC <= 8 ? 3 : 2; }
+constexpr int kQkGroup = 3;     // chunks whose K reads and bias are in flight together
 
 // Workgroup b does part b / G of unit b % G: the unit's tiles are dealt to the
 // wavefronts of its p.split workgroups in turn, each of which stages V^T and K.
-template <int NC, int DTMAX, bool HALF, bool FP, int DK, bool P0 = false>
+// BIAS: the call has a bias.  With both forms of the logits in one kernel, the
+// 8 NC registers where the two met were copied and spilled (577 keys, dk = d =
+// 64: 352 bytes of scratch a lane, most of it written and read in the tile
+// loop).  256 units of 577 x 577, dk = d = 64: 82 -> 68 us, with a bias 142 ->
+// 90 us.
+template <int NC, int DTMAX, bool HALF, bool FP, int DK, bool P0, bool BIAS>
 __global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_qk_kernel(
     LisArgs a, QkArgs qa, LisLaunch p) {
     constexpr int WAVES = qk_waves(NC);
@@ -273,7 +302,7 @@ __global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_
     __syncthreads();
 
     const int8_t* q_base = qa.q + g * (int64_t)a.Lq * DK;
-    const int32_t* bplane = a.bias ? a.bias + (g % a.Hb) * (int64_t)a.Lq * a.Lk : nullptr;
+    const int32_t* bplane = BIAS ? a.bias + (g % a.Hb) * (int64_t)a.Lq * a.Lk : nullptr;
 
     i32x4v qb[DK >= 64 ? DK / 64 : 1];
     int64_t qb8 = 0;
@@ -284,20 +313,31 @@ __global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_
         const int i0 = 16 * tile;
         const int i = min(i0 + r, a.Lq - 1);
 
-        // logits of this tile in the Log-Int-Softmax lane layout, with or
-        // without a bias (uniform; two bodies, since one that adds the bias
-        // under a branch copies every logit)
+        // Logits of this tile in the Log-Int-Softmax lane layout, kQkGroup chunks
+        // at a time: a few chunks' K reads in flight, not all, and the bias of
+        // the next group requested before this one waits for its own.
         int lg[NC][8];
-        auto logits = [&](const int32_t* brow) __attribute__((always_inline)) {
+        i32x4v bias[2][kQkGroup][2];
+        const int32_t* brow = BIAS ? bplane + (int64_t)i * a.Lk : nullptr;
+        auto request = [&](int c0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                qk_chunk<DK, HALF>(lg[c], kst, ck, qb, qb8, brow, c, r, kg, a.Lk, c == NC - 1);
-                // long rows: a few chunks' K reads in flight, not all
-                if (NC > kQkRegsNC && c % 3 == 2) __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int u = 0; u < kQkGroup; ++u)
+                if (BIAS && c0 + u < NC)
+                    qk_load_bias(bias[c0 / kQkGroup % 2][u], brow, c0 + u, kg, a.Lk, c0 + u == NC - 1);
         };
-        if (bplane) logits(bplane + (int64_t)i * a.Lk);
-        else logits(nullptr);
+        request(0);
+#pragma unroll
+        for (int c0 = 0; c0 < NC; c0 += kQkGroup) {
+            request(c0 + kQkGroup);
+#pragma unroll
+            for (int u = 0; u < kQkGroup; ++u) {
+                const int c = c0 + u;
+                if (c < NC)
+                    qk_chunk<DK, HALF, BIAS>(lg[c], kst, ck, qb, qb8, bias[c0 / kQkGroup % 2][u], c, r, kg,
+                                             a.Lk, c == NC - 1);
+            }
+            if (NC > kQkRegsNC) __builtin_amdgcn_sched_barrier(0);
+        }
         // the next tile's query bytes, in flight during the rest of this tile
         qk_load_q<DK>(q_base, min(16 * (tile + step < p.ntiles ? tile + step : tile) + r, a.Lq - 1), kg,
                       qb, qb8);
@@ -326,8 +366,8 @@ __global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_
             }
             if constexpr (NC > kQkRegsNC) {
                 if (__builtin_expect(todo != 0, 0))
-                    qk_fix_chunks<NC, DTMAX, DK, P0>(acc, todo, kst, ck, vt, p.ld, q_base, i,
-                                                     bplane ? bplane + (int64_t)i * a.Lk : nullptr, st,
+                    qk_fix_chunks<NC, DTMAX, DK, P0, BIAS>(acc, todo, kst, ck, vt, p.ld, q_base, i,
+                                                     BIAS ? bplane + (int64_t)i * a.Lk : nullptr, st,
                                                      k, a.Lk, r, kg);
             }
         } else {
@@ -354,27 +394,30 @@ template <int DK, int NC>
 hipError_t launch_qk_nc(int dtm, bool half, int fpm, const LisArgs& a, const QkArgs& qa,
                         const LisLaunch& p, size_t lds, hipStream_t stream) {
     const dim3 grid((unsigned)(a.G * p.split)), block(64 * qk_waves(NC));
-#define FQ_QK(DT, H, F, P0) \
-    launch_kernel(lis_qk_kernel<NC, DT, H, F, DK, P0>, grid, block, lds, stream, a, qa, p)
+#define FQ_QK(DT, H, F, P0)                                                                   \
+    do {                                                                                          \
+        if (a.bias)                                                                               \
+            launch_kernel(lis_qk_kernel<NC, DT, H, F, DK, P0, true>, grid, block, lds, stream, a, qa, p);  \
+        else                                                                                      \
+            launch_kernel(lis_qk_kernel<NC, DT, H, F, DK, P0, false>, grid, block, lds, stream, a, qa, p); \
+    } while (0)
+#define FQ_QK_F(DT, H)                          \
+    if (fpm == 2) FQ_QK(DT, H, true, true);     \
+    else FQ_QK(DT, H, true, false)
     if constexpr (NC > kQkRegsNC) {
-        if (dtm == 2) {
-            if (fpm == 2) FQ_QK(2, false, true, true);
-            else FQ_QK(2, false, true, false);
-        } else {
-            if (fpm == 2) FQ_QK(4, false, true, true);
-            else FQ_QK(4, false, true, false);
-        }
+        if (dtm == 2) { FQ_QK_F(2, false); }
+        else { FQ_QK_F(4, false); }
     } else {
-#define FQ_QK_F(DT, H) \
-    if (fpm == 2) FQ_QK(DT, H, true, true); else if (fpm == 1) FQ_QK(DT, H, true, false); \
-    else FQ_QK(DT, H, false, false)
-#define FQ_QK_H(DT) \
-    if (half) { FQ_QK_F(DT, true); } else { FQ_QK_F(DT, false); }
-        if (dtm == 2) { FQ_QK_H(2) }
-        else { FQ_QK_H(4) }
+#define FQ_QK_H(DT, H) \
+    if (fpm == 0) FQ_QK(DT, H, false, false); else FQ_QK_F(DT, H)
+        if (dtm == 2) {
+            if (half) { FQ_QK_H(2, true); } else { FQ_QK_H(2, false); }
+        } else {
+            if (half) { FQ_QK_H(4, true); } else { FQ_QK_H(4, false); }
+        }
 #undef FQ_QK_H
-#undef FQ_QK_F
     }
+#undef FQ_QK_F
 #undef FQ_QK
     return hipGetLastError();
 }

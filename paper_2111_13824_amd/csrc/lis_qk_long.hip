@@ -45,7 +45,7 @@ __device__ __forceinline__ void long_stage_vt(uint16_t* vt, int ld, const int8_t
     }
 }
 
-template <int DTMAX, int DK>
+template <int DTMAX, int DK, bool BIAS>
 __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, QkArgs qa,
                                                                    LisLaunch p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, Qk
     __syncthreads();
 
     const int8_t* q_base = qa.q + g * (int64_t)a.Lq * DK;
-    const int32_t* bplane = a.bias ? a.bias + (g % a.Hb) * (int64_t)a.Lq * Lk : nullptr;
+    const int32_t* bplane = BIAS ? a.bias + (g % a.Hb) * (int64_t)a.Lq * Lk : nullptr;
     for (int tile = wave + kQkLongWaves * part; tile < p.ntiles; tile += kQkLongWaves * p.split) {
         const int i0 = 16 * tile;
         const int i = min(i0 + r, a.Lq - 1);
@@ -83,8 +83,8 @@ __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, Qk
         qb[0] = i32x4v{0, 0, 0, 0};
         qk_load_q<DK>(q_base, i, kg, qb, qb8);
         f32x4 acc[DTMAX];
-        qk_tile_passes<DTMAX, DK>(acc, kst, ck, vt, p.ld, qb, qb8,
-                                  bplane ? bplane + (int64_t)i * Lk : nullptr, k, nc, Lk, r, kg);
+        qk_tile_passes<DTMAX, DK, BIAS>(acc, kst, ck, vt, p.ld, qb, qb8,
+                                        BIAS ? bplane + (int64_t)i * Lk : nullptr, k, nc, Lk, r, kg);
         store_out_t<DTMAX>(acc, a, g, i0, r, kg, p.out_vec);
     }
 }
@@ -92,7 +92,13 @@ __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, Qk
 hipError_t launch_qk_long_int(int dk, int dtm, const LisArgs& a, const QkArgs& qa,
                               const LisLaunch& p, size_t lds, hipStream_t stream) {
     const dim3 grid((unsigned)(a.G * p.split)), block(kQkLongBlock);
-#define FQ_QKL(DT, DK) launch_kernel(lis_qk_long_kernel<DT, DK>, grid, block, lds, stream, a, qa, p)
+#define FQ_QKL(DT, DK)                                                                            \
+    do {                                                                                          \
+        if (a.bias)                                                                               \
+            launch_kernel(lis_qk_long_kernel<DT, DK, true>, grid, block, lds, stream, a, qa, p);  \
+        else                                                                                      \
+            launch_kernel(lis_qk_long_kernel<DT, DK, false>, grid, block, lds, stream, a, qa, p); \
+    } while (0)
     if (dk == 32) {
         if (dtm == 2) FQ_QKL(2, 32);
         else FQ_QKL(4, 32);
