@@ -336,11 +336,12 @@ __global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_
                     qk_chunk<DK, HALF, BIAS>(lg[c], kst, ck, qb, qb8, bias[c0 / kQkGroup % 2][u], c, r, kg,
                                              a.Lk, c == NC - 1);
             }
-            if (NC > kQkRegsNC) __builtin_amdgcn_sched_barrier(0);
+            if (NC > kQkRegsNC || !FP) __builtin_amdgcn_sched_barrier(0);
         }
         // the next tile's query bytes, in flight during the rest of this tile
-        qk_load_q<DK>(q_base, min(16 * (tile + step < p.ntiles ? tile + step : tile) + r, a.Lq - 1), kg,
-                      qb, qb8);
+        // (integer path: requested at its end, where its registers are free)
+        const int nt = min(16 * (tile + step < p.ntiles ? tile + step : tile) + r, a.Lq - 1);
+        if (FP) qk_load_q<DK>(q_base, nt, kg, qb, qb8);
         f32x4 acc[DTMAX];
 #pragma unroll
         for (int dt = 0; dt < DTMAX; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -383,6 +384,7 @@ __global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        if (!FP) qk_load_q<DK>(q_base, nt, kg, qb, qb8);
         store_out_t<DTMAX>(acc, a, g, i0, r, kg, p.out_vec);
     }
 }

@@ -65,3 +65,17 @@ def test_qk_long_rows_hold_their_logits(scratch):
     bad = {n: s for n, s in _spilling(scratch, "lis_qk_kernel").items()
            if n.split("<")[1].split(",")[3].strip() == "true"}
     assert not bad, bad
+
+
+def test_qk_integer_rows_of_197_keys_hold_their_state(scratch):
+    """The integer path holds a 32-bit and an 8-bit value per key: rows of 193
+    to 208 keys without a bias (seven chunks, the last one half) fit the
+    registers of three wavefronts per SIMD, full rows of 224 nearly do."""
+    spill = {n: s for n, s in scratch.items()
+             if n.startswith("lis_qk_kernel<") and n.split(",")[3].strip() == "false"}
+    assert spill
+    for n, s in spill.items():
+        args = [x.strip(" >") for x in n.split("<")[1].split(",")]
+        nc, half, bias = int(args[0]), args[2] == "true", args[6] == "true"
+        limit = 0 if nc < 7 or (half and not bias) else 80
+        assert s <= limit, (n, s)
