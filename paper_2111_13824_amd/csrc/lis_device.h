@@ -577,8 +577,13 @@ __device__ __forceinline__ int32_t screen_c(int mx, const LisConsts& k) {
     return (int32_t)((uint32_t)mx - (k.d_ln2 - 1u) - (uint32_t)kFloat23);
 }
 
-// P0: the pre-shift is known to be 0 (d > 512).
-template <bool P0 = false>
+// P0: the pre-shift is known to be 0 (d > 512).  INPLACE: the result in v's own
+// register.  A row's logits come in fours (a 16-byte load, an MFMA's result),
+// whose registers are adjacent; with each e anywhere else, the next tile's
+// loads find no four adjacent ones free, and rows of more than 480 keys spilled
+// (577 keys, d = 64: 256 registers and 68 bytes a lane; 200 and none in place:
+// 256 units 110.7 -> 98.6 us).
+template <bool P0 = false, bool INPLACE = false>
 __device__ __forceinline__ uint32_t screen_iexp(int v, int32_t c, const LisConsts& k) {
     const int32_t lo = kFloat23 - (int32_t)(k.u_max - k.d_ln2 + 1u);
     const int32_t a = max((int32_t)((uint32_t)v - (uint32_t)c), lo);
@@ -590,6 +595,10 @@ __device__ __forceinline__ uint32_t screen_iexp(int v, int32_t c, const LisConst
     const float w = __int_as_float(f) + k.s_add;
     const float qL = __builtin_fmaf(w, w, k.s_qc);
     // bits(qL) - z 2^23: z <= 30 and qL >= 1, so the result stays normal
+    if (INPLACE) {
+        asm("v_lshl_add_u32 %0, %1, 23, %2" : "+v"(v) : "v"(nz), "v"(qL));
+        return (uint32_t)v;
+    }
     return ((uint32_t)nz << 23) + __float_as_uint(qL);
 }
 
@@ -731,7 +740,7 @@ __device__ __forceinline__ ScreenRow tile_iexp_screen(int (&lg)[NC][8], const Li
             }
             int v = lg[c][t];
             if (NC > 7) asm volatile("" : "+v"(v));      // as in chunk_pbits_screen
-            uint32_t b = screen_iexp<P0>(v, mc, k);
+            uint32_t b = NC > 7 && c < NC - 1 ? screen_iexp<P0, true>(v, mc, k) : screen_iexp<P0>(v, mc, k);
             if (c == NC - 1) b = v != INT_MIN ? b : 0u;
             lg[c][t] = (int)b;
             e[t] = __uint_as_float(b);

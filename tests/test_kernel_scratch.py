@@ -79,3 +79,9 @@ def test_qk_integer_rows_of_197_keys_hold_their_state(scratch):
         nc, half, bias = int(args[0]), args[2] == "true", args[6] == "true"
         limit = 0 if nc < 7 or (half and not bias) else 80
         assert s <= limit, (n, s)
+
+
+def test_unit_kernels_hold_their_rows(scratch):
+    """The unit kernel (fused head and stored codes): no instance spills."""
+    bad = _spilling(scratch, "lis_unit_kernel")
+    assert not bad, bad
