@@ -1197,12 +1197,6 @@ __device__ __forceinline__ void unit_begin(int (&lg)[NC][8], const UnitPlanes& u
 // so the next tile is in flight without holding two tiles in registers.
 constexpr int kUnitTwoBufNC = 7;     // rows whose tiles alternate between two buffers
 constexpr int kUnitShortNC = 7;      // rows instantiated with half last chunks (lis_inst_unit.hip)
-// Output of rows of 15 chunks and more by transposed blocks straight from the
-// registers (as the Q K kernel): the row-wise stores through LDS made them
-// spill (256 units of 577 x 577: 127.5 us with, 117.8 us without); up to 14
-// chunks the whole-row stores are the better ones (300 units of 400 x 400: 86.0
-// against 89.4 us).
-constexpr bool unit_transposed(int NC) { return NC >= 15; }
 constexpr int unit_prefetch(int NC, bool FUSED, int DTMAX, bool HALF) {
     return FUSED && NC >= 5 && NC <= kUnitTwoBufNC && !(NC == 7 && DTMAX == 4 && !HALF) ? 2 : 0;
 }
@@ -1293,7 +1287,6 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
                                           uint32_t valid) {
     constexpr int NT = HALF ? 4 : 8;
     constexpr int PF = unit_prefetch(NC, FUSED, DTMAX, HALF);
-    constexpr bool TR = unit_transposed(NC);
     const int i0 = 16 * tile;
     unit_begin<NC, HALF>(cur, up, unit_off(min(i0 + r, a.Lq - 1), a.Lk, kg), valid);
     const int nt = tile + step;
@@ -1317,16 +1310,15 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
             u32x4 pb = chunk_pbits_screen<NC, NT, true>(cur, st, c, undecided);
             if (__builtin_expect(undecided, 0)) pb = chunk_pbits_exact_lds(cur[c], k, scr, lane);
             if (HALF && c == NC - 1)
-                chunk_mfma<DTMAX, true, TR>(acc, pb, vt, p.ld, c, r, kg);
+                chunk_mfma<DTMAX, true>(acc, pb, vt, p.ld, c, r, kg);
             else
-                chunk_mfma<DTMAX, false, TR>(acc, pb, vt, p.ld, c, r, kg);
+                chunk_mfma<DTMAX, false>(acc, pb, vt, p.ld, c, r, kg);
             if (PF + c < NC) next_chunk(PF + c);
             // keep each chunk's V^T reads next to its MFMAs (hoisting them all
             // would take 4 DTMAX registers per chunk)
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (TR) store_out_t<DTMAX>(acc, a, g, i0, r, kg, p.out_vec);
-        else if (p.out_vec) store_out_rows<DTMAX>(acc, ot, a, g, i0, lane, r, kg);
+        if (p.out_vec) store_out_rows<DTMAX>(acc, ot, a, g, i0, lane, r, kg);
         else store_out<DTMAX>(acc, a, g, i0, r, kg);
         return;
     }
