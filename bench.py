@@ -58,7 +58,8 @@ PAPER_CONTEXT = {
     "vit_b_gbitops_8_8_4_ptf_lis": 1117.76,
 }
 LIS_SOURCES = ["lis_device.h", "lis_attention.hip", "lis_inst_lo.hip", "lis_inst_hi.hip",
-               "lis_inst_unit.hip", "lis_unit_long.hip", "fqvit_internal.h", "fqvit_launch.h"]
+               "lis_inst_unit.hip", "lis_unit_long.hip", "lis_dispatch.h", "fqvit_internal.h",
+               "fqvit_launch.h"]
 
 
 def _code_only(text):

@@ -327,102 +327,23 @@ void launch_stream(bool fused, int dt, dim3 grid, size_t lds, hipStream_t stream
 
 }  // namespace
 
-// LDS of one workgroup on gfx950.
-constexpr size_t kMaxLdsBytes = 160 * 1024;
-
-// Wavefronts per unit of the unit kernel: units of at most four 16-row tiles
-// (and rows of at most four chunks, whose V^T 64 threads can stage) get one
-// wavefront per tile up to two, so that the per-wavefront set-up serves
-// several tiles.  Measured on Swin-S (6144 units of 49 x 49, d = 32): two
-// wavefronts per unit 41.4 us, one 43.7 us, four 46.6-47.3 us.
-int unit_waves(int nc, int tiles16) {
-    if (nc > 4 || tiles16 > 4) return lis::unit_long_waves(nc);
-    return tiles16 == 1 ? 1 : 2;
-}
-
 hipError_t launch_lis(const LisArgs& a, hipStream_t stream) {
     using namespace lis;
-    const bool fused = a.out != nullptr;
-    LisLaunch p;
-    p.ntiles = (a.Lq + kRowsPerBlock - 1) / kRowsPerBlock;
-    const int nc = (a.Lk + 31) / 32;
-    // V^T columns padded to a power of two, at least 32 (two MFMA tiles).
-    int dt = 2;
-    while (fused && 16 * dt < a.d) dt <<= 1;
-    p.dpad = 16 * dt;
-    p.ncg = dt;
-    const int max_keys = vt_stage_keys(p.dpad);
-    p.kb = std::max(32, std::min(nc * 32, max_keys));
-    p.ld = p.kb + 8;
-    p.vec_ok = fused && (a.d % 16 == 0) && ((reinterpret_cast<uintptr_t>(a.v) & 15) == 0);
-    p.vt_bytes = fused ? p.dpad * p.ld * (int)sizeof(uint16_t) : 0;
-    p.out_vec = fused && (a.d % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.out) & 15) == 0);
-    // LDS of the row-wise output stores: one 16 x (dpad + 4) int32 block per wavefront
-    const size_t out_lds = p.out_vec ? (size_t)4 * 16 * (p.dpad + 4) * sizeof(int32_t) : 0;
-    // the unit kernel's region per wavefront, which an undecided chunk also uses
-    const size_t unit_lds = fused ? (size_t)unit_lds_dwords(dt) * sizeof(int32_t) : 0;
-    p.n_logits = a.G * (int64_t)a.Lq * a.Lk;
-    p.n_bias = a.bias ? (int64_t)a.Hb * a.Lq * a.Lk : 0;
-    p.split = 1;
-    p.codes_ldw = 0;
-    const int64_t blocks = a.G * (int64_t)p.ntiles;
-    const dim3 grid((unsigned)blocks);
-    const bool fp = a.k.fp_ok != 0;
-    // Unit kernel: rows of up to 640 keys on the float path; the fused product
-    // for d <= 64 and no codes output; codes only of more than 224 keys for
-    // dense code rows.
-    const int tiles16 = (a.Lq + 15) / 16;
-    const bool half = a.Lk - 32 * (nc - 1) <= 16;
-    const int row_bytes = a.k.top > 15 ? a.Lk : (a.Lk + 1) / 2;
-    const bool dense = !fused && a.ld_codes == row_bytes;
-    const bool unit_ok = fp && a.G <= 0x7FFFFFFF && (int64_t)a.Lq * a.Lk < ((int64_t)1 << 29) &&
-                         nc <= kUnitMaxNC &&
-                         (fused ? a.codes == nullptr && dt <= 4 : dense || nc <= kUnitShortNC);
-    if (unit_ok) {
-        LisLaunch u = p;
-        u.ntiles = tiles16;
-        u.kb = nc * 32;
-        u.ld = u.kb + 8;
-        u.vt_bytes = fused ? u.dpad * u.ld * (int)sizeof(uint16_t) : 0;
-        const int wpu = unit_waves(nc, tiles16);
-        size_t lds = (size_t)u.vt_bytes +
-                     (fused ? unit_lds : (size_t)kScreenLds * sizeof(int32_t)) * wpu;
-        // codes only, dense rows: each wavefront gathers its tile's code rows
-        // in LDS and writes them as one span
-        if (dense) {
-            u.codes_ldw = (16 * row_bytes + 8 + 15) / 16 * 16;
-            lds += (size_t)wpu * u.codes_ldw;
-        }
-        // Workgroups per unit: a unit is dealt to as many as fill the workgroup
-        // slots of 256 CUs, at most one tile a wavefront (each stages V^T; see launch_lis_qk).  Measured against a workgroup per unit: 6
-        // units of 577 x 577, d = 48, 85 -> 24 us; 30 of them with a bias 122
-        // -> 36 us; 90 units of 325 x 325 with a bias 47 -> 26 us.
-        const int64_t slots =
-            256 * std::max<int64_t>(1, std::min<int64_t>(12 / wpu, kMaxLdsBytes / std::max<size_t>(lds, 1)));
-        const int64_t most = (tiles16 + wpu - 1) / wpu;
-        u.split = (int)std::max<int64_t>(1, std::min<int64_t>(most, slots / a.G));
-        // One tile a wavefront: the tile kernel, whose rows stay in place (12
-        // units of 116 x 116 with a bias 6.2 us, 7.2 us in the unit kernel; 96
-        // units of 256 x 256 13.5 and 14.1 us).
-        const bool single = u.split == most && slots >= a.G && (!fused || nc <= kRegsFusedMaxNC);
-        if (!single && nc > kUnitShortNC)
-            return nc <= 14 ? launch_lis_unit_lo(nc, fused, dt, a, u, lds, stream)
-                            : launch_lis_unit_hi(nc, fused, dt, a, u, lds, stream);
-        if (!single) return launch_lis_unit(nc, fused, dt, half, wpu, a, u, lds, stream);
+    const LisPlan s = plan_lis(a);
+    if (s.kernel == LisPlan::kUnit) {
+        if (s.nc <= kUnitShortNC)
+            return launch_lis_unit(s.nc, s.fused, s.dt, s.half, s.waves, a, s.p, s.lds, stream);
+        return s.nc <= 14 ? launch_lis_unit_lo(s.nc, s.fused, s.dt, a, s.p, s.lds, stream)
+                          : launch_lis_unit_hi(s.nc, s.fused, s.dt, a, s.p, s.lds, stream);
     }
-    // Tile kernels: codes only for rows of up to 640 keys, the fused product on
-    // the integer path (without a codes output, d <= 64) for rows of up to 288.
-    const bool regs = fused ? (nc <= kRegsFusedMaxNC && a.codes == nullptr && dt <= 4) : nc <= 20;
-    if (regs) {
-        const size_t lds = (size_t)p.vt_bytes + out_lds;
-        return nc <= 10 ? launch_lis_regs_lo(nc, fused, dt, fp, a, p, grid, lds, stream)
-                        : launch_lis_regs_hi(nc, fused, dt, fp, a, p, grid, lds, stream);
-    }
-    const size_t lds = fused ? (size_t)p.vt_bytes : 0;
-    if (fp)
-        launch_stream<true>(fused, dt, grid, lds, stream, a, p);
+    const dim3 grid((unsigned)s.blocks);
+    if (s.kernel == LisPlan::kTile)
+        return s.nc <= 10 ? launch_lis_regs_lo(s.nc, s.fused, s.dt, s.fp, a, s.p, grid, s.lds, stream)
+                          : launch_lis_regs_hi(s.nc, s.fused, s.dt, s.fp, a, s.p, grid, s.lds, stream);
+    if (s.fp)
+        launch_stream<true>(s.fused, s.dt, grid, s.lds, stream, a, s.p);
     else
-        launch_stream<false>(fused, dt, grid, lds, stream, a, p);
+        launch_stream<false>(s.fused, s.dt, grid, s.lds, stream, a, s.p);
     return hipGetLastError();
 }
 

@@ -50,12 +50,10 @@
 #include <utility>
 
 #include "fqvit_launch.h"
+#include "lis_dispatch.h"
 
 namespace fqvit {
 namespace lis {
-
-constexpr int kBlock = 256;        // four wavefronts
-constexpr int kRowsPerBlock = 64;  // 16 rows per wavefront in the tile kernel
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -346,26 +344,6 @@ __device__ __forceinline__ void store_codes_row(uint8_t* crow, int Lk, int top, 
         store_codes<FULL>(crow, (Lk + 1) >> 1, c, kg, code);
     }
 }
-
-// Keys of V^T per LDS stage for a padded head dimension dpad: at most 40 KB of
-// LDS per workgroup so that several workgroups share a CU.
-constexpr int vt_stage_keys(int dpad) { return (40960 / (2 * dpad) - 8) / 32 * 32; }
-
-struct LisLaunch {
-    int ntiles;     // tile kernel: row tiles of 64 per unit; unit kernel: 16-row tiles per unit
-    int kb;         // keys per V^T stage (multiple of 32)
-    int ld;         // LDS row stride of V^T in bf16 elements
-    int dpad;       // 16 * (power of two >= ceil(d / 16))
-    int ncg;        // dpad / 16: 16-column groups of V
-    int vec_ok;     // V rows read as 16-byte vectors (d % 16 == 0, 16-byte aligned V)
-    int vt_bytes;   // LDS bytes of one V^T stage (0 for codes only)
-    int out_vec;    // output rows written through LDS as 16-byte units (d % 4 == 0, aligned out)
-    int64_t n_logits;  // elements of the logits tensor (G Lq Lk)
-    int64_t n_bias;    // elements of the bias tensor (Hb Lq Lk), 0 without bias
-    int split;         // workgroups per unit (unit and Q K kernels)
-    int codes_ldw;     // unit kernel, codes only: LDS bytes per wavefront of the tile's
-                       // code rows (dense rows, ld_codes = row bytes), 0: direct stores
-};
 
 // ---------------------------------------------------------------------------
 // Integer path
@@ -1041,15 +1019,6 @@ __device__ __forceinline__ void store_out(const f32x4 (&acc)[DTMAX], const LisAr
 template <int DTMAX>
 constexpr int out_lds_dwords() { return 16 * (16 * DTMAX + 4); }
 
-// LDS dwords of an undecided chunk's keys and the row sums (64 x 8 + 64 x 2).
-constexpr int kScreenLds = 640;
-
-// The fused unit kernel's LDS per wavefront: that block, or kScreenLds dwords
-// where it is smaller.
-constexpr int unit_lds_dwords(int dtm) {
-    return 16 * (16 * dtm + 4) > kScreenLds ? 16 * (16 * dtm + 4) : kScreenLds;
-}
-
 template <int DTMAX>
 __device__ __forceinline__ void store_out_rows(const f32x4 (&acc)[DTMAX], int32_t* ot,
                                                const LisArgs& a, int64_t g, int i0, int lane,
@@ -1196,7 +1165,6 @@ __device__ __forceinline__ void unit_begin(int (&lg)[NC][8], const UnitPlanes& u
 // the current tile has gone through its MFMA (its registers are free by then),
 // so the next tile is in flight without holding two tiles in registers.
 constexpr int kUnitTwoBufNC = 7;     // rows whose tiles alternate between two buffers
-constexpr int kUnitShortNC = 7;      // rows instantiated with half last chunks (lis_inst_unit.hip)
 constexpr int unit_prefetch(int NC, bool FUSED, int DTMAX, bool HALF) {
     return FUSED && NC >= 5 && NC <= kUnitTwoBufNC && !(NC == 7 && DTMAX == 4 && !HALF) ? 2 : 0;
 }
@@ -1562,13 +1530,6 @@ __global__ __launch_bounds__(kBlock, lis_waves_per_simd(NC)) void lis_kernel(Lis
 
 // Launch of the tile kernel for exactly NC chunks; the host has checked that
 // dtm is 2 or 4 for fused calls (d <= 64).  MULTI follows from NC and dtm.
-// Longest rows (in 32-key chunks) of the fused tile kernels.  Beyond 9 chunks
-// the stream kernel, which re-reads the logits instead of holding them, is
-// faster (d = 64, 64 square units, on one MI355X: 300 keys 30 against 36 us,
-// 384 keys 41 against 61 us); up to 9 chunks the tile kernels are (288 keys
-// 15 against 29 us, 240 keys 10 against 19 us).
-constexpr int kRegsFusedMaxNC = 9;
-
 template <int NC>
 hipError_t launch_lis_nc(bool fused, int dtm, bool fp, const LisArgs& a, const LisLaunch& p,
                          dim3 grid, size_t lds, hipStream_t s) {
@@ -1593,12 +1554,6 @@ hipError_t launch_lis_nc(bool fused, int dtm, bool fp, const LisArgs& a, const L
 }
 
 // Launch of the unit kernel for exactly NC chunks (NC <= kUnitMaxNC).
-constexpr int kUnitMaxNC = 20;
-// Wavefronts per workgroup of rows of more than four chunks: up to 10 chunks
-// several workgroups share a CU's LDS, beyond one takes it (V^T of 577 keys and
-// d = 64: 79 KB).
-constexpr int unit_long_waves(int NC) { return NC <= 10 ? 4 : 8; }
-
 template <int NC, int WPU>
 hipError_t launch_unit_nc_w(bool fused, int dtm, bool half, const LisArgs& a, const LisLaunch& p,
                             size_t lds, hipStream_t s) {

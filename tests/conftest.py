@@ -19,3 +19,10 @@ def orc():
     import oracle
     oracle.build(force=False)
     return oracle
+
+
+@pytest.fixture(scope="session")
+def plan(tmp_path_factory):
+    """What a Log-Int-Softmax call launches (tests/launch_plan.py)."""
+    from launch_plan import Launches
+    return Launches(tmp_path_factory.mktemp("plan"))
