@@ -701,8 +701,8 @@ __device__ __forceinline__ RowState screen_exact(double S, const LisConsts& k) {
 // keys of the last chunk).  EXACT: the row sum S is exact (every key added in
 // binary64, 5 cycles more a key); kernels that overwrite a chunk's e before the
 // last chunk is decided need it, the others take the sum again (screen_sum)
-// when a chunk is undecided.
-template <int NC, int NT, bool EXACT, bool P0 = false>
+// when a chunk is undecided.  INPLACE: see screen_iexp.
+template <int NC, int NT, bool EXACT, bool P0 = false, bool INPLACE = (NC > 7)>
 __device__ __forceinline__ ScreenRow tile_iexp_screen(int (&lg)[NC][8], const LisConsts& k,
                                                       double& S) {
     const int32_t mc = screen_c(tile_max<NC>(lg), k);
@@ -717,8 +717,8 @@ __device__ __forceinline__ ScreenRow tile_iexp_screen(int (&lg)[NC][8], const Li
                 continue;
             }
             int v = lg[c][t];
-            if (NC > 7) asm volatile("" : "+v"(v));      // as in chunk_pbits_screen
-            uint32_t b = NC > 7 && c < NC - 1 ? screen_iexp<P0, true>(v, mc, k) : screen_iexp<P0>(v, mc, k);
+            if (INPLACE) asm volatile("" : "+v"(v));     // as in chunk_pbits_screen
+            uint32_t b = INPLACE && c < NC - 1 ? screen_iexp<P0, true>(v, mc, k) : screen_iexp<P0>(v, mc, k);
             if (c == NC - 1) b = v != INT_MIN ? b : 0u;
             lg[c][t] = (int)b;
             e[t] = __uint_as_float(b);
@@ -1294,7 +1294,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
     // of 577 x 577 24 us less than in the tile kernel).  ot: the code rows'
     // region, then an undecided chunk's.
     double S;
-    const ScreenRow st = tile_iexp_screen<NC, NT, true>(cur, k, S);
+    const ScreenRow st = tile_iexp_screen<NC, NT, true, false, true>(cur, k, S);
     uint32_t* scr = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(ot) + p.codes_ldw);
     *reinterpret_cast<double*>(scr + 512 + 2 * lane) = S;
     const int i = i0 + r;
@@ -1303,7 +1303,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
         chunk_codes_screen<NC, NT>(code, cur, st, k, c, undecided);
         if (__builtin_expect(undecided, 0)) chunk_codes_exact_lds(code, cur[c], k, scr, lane);
     };
-    if (NC > kUnitShortNC || p.codes_ldw != 0) {    // (long rows: always dense)
+    if constexpr (DTMAX == 1) {
         // Dense code rows: the tile's rows are one contiguous span of the codes
         // tensor.  They are gathered in LDS at the span's offset from a dword
         // boundary (mis; a row past Lq is gathered but not written), then
@@ -1350,19 +1350,19 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
 }
 
 // Minimum wavefronts per SIMD the register allocation is held to (the second
-// argument of __launch_bounds__): three for four wavefronts per unit (168
-// registers); for the small units that take one or two, six where the kernel
-// fits 80 registers (codes-only rows of one chunk), so that as many units are
-// in flight as the CU holds, five for fused rows of up to two chunks with
-// d <= 32 (96 registers: with the one-row tile path they spilled at 80; on
-// the Swin-S shapes five and six measured the same without it), and four
-// otherwise (128 registers).
-// Rows of more than 8 chunks hold more logits than three wavefronts per SIMD
-// leave registers for: two.
+// argument of __launch_bounds__).  Fused: three for four wavefronts per unit
+// (168 registers); for the small units that take one or two, five for rows of
+// up to two chunks with d <= 32 (96 registers: with the one-row tile path they
+// spilled at 80; on the Swin-S shapes five and six measured the same without
+// it), and four otherwise (128 registers); rows of more than 8 chunks hold more
+// logits than three wavefronts per SIMD leave registers for: two.  Codes only:
+// what the rows need by themselves (seven chunks: 94 registers).
 constexpr int unit_waves_per_simd(int NC, bool FUSED, int DTMAX, int WPU) {
-    return NC > 8 ? 2 : WPU == 4 ? 3 : (FUSED && NC <= 2 && DTMAX <= 2 ? 5 : (!FUSED && NC <= 1) ? 6 : 4);
+    if (!FUSED) return NC <= 2 ? 6 : NC <= 10 ? 4 : NC <= 16 ? 3 : 2;
+    return NC > 8 ? 2 : WPU == 4 ? 3 : NC <= 2 && DTMAX <= 2 ? 5 : 4;
 }
 
+// Workgroup (g, part): part of unit g.
 // WPU wavefronts per unit (4, or fewer for units of few tiles, so that each
 // wavefront walks several; V^T staged by those 64 WPU threads).
 template <int NC, bool FUSED, int DTMAX, bool HALF, int WPU = 4>
@@ -1370,8 +1370,8 @@ __global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, WPU
     LisArgs a, LisLaunch p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint16_t* vt = reinterpret_cast<uint16_t*>(smem);
-    const int part = (int)(blockIdx.x / (unsigned)a.G);
-    const int64_t g = blockIdx.x - (unsigned)part * (unsigned)a.G;
+    const int part = (int)blockIdx.y;
+    const int64_t g = blockIdx.x;
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
@@ -1395,7 +1395,8 @@ __global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, WPU
     const int ntl = kRow1 && (a.Lq & 15) == 1 ? p.ntiles - 1 : p.ntiles;
     int bufA[NC][8], bufB[NC][8];
     const int step = WPU * p.split;
-    int tile = (wave + WPU * part + (int)(g % WPU)) % step;
+    int tile = wave + WPU * part + (int)(g % WPU);
+    tile = tile < step ? tile : tile - step;
     unit_load_range<NC, HALF, 0, NC>(
         bufA, up, unit_off(tile < ntl ? min(16 * tile + r, a.Lq - 1) : -1, a.Lk, kg));
     const uint32_t valid = last_valid<NC>(kg, a.Lk);
@@ -1409,7 +1410,7 @@ __global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, WPU
     // Rows of more than seven chunks load each chunk of the next tile into the
     // registers of the one just consumed: one body of code (two of 577 keys
     // outgrow the instruction cache: 142.5 against 128.0 us on 256 units).
-    if constexpr (NC > kUnitTwoBufNC) {
+    if constexpr (!FUSED || NC > kUnitTwoBufNC) {
         for (; tile < ntl; tile += step)
             unit_tile<NC, FUSED, DTMAX, HALF>(bufA, bufA, a, p, k, vt, ot, up, g, tile, step, ntl, lane, r,
                                               kg, valid);
@@ -1555,18 +1556,14 @@ hipError_t launch_lis_nc(bool fused, int dtm, bool fp, const LisArgs& a, const L
 
 // Launch of the unit kernel for exactly NC chunks (NC <= kUnitMaxNC).
 template <int NC, int WPU>
-hipError_t launch_unit_nc_w(bool fused, int dtm, bool half, const LisArgs& a, const LisLaunch& p,
+hipError_t launch_unit_nc_w(int dtm, bool half, const LisArgs& a, const LisLaunch& p,
                             size_t lds, hipStream_t s) {
 #define FQ_UNIT(FUSED, DTM, HALF)                                                       \
-    launch_kernel(lis_unit_kernel<NC, FUSED, DTM, HALF, WPU>, dim3((unsigned)(a.G * p.split)), \
-                  dim3(64 * WPU), lds, s, a, p)
+    launch_kernel(lis_unit_kernel<NC, FUSED, DTM, HALF, WPU>,                           \
+                  dim3((unsigned)a.G, (unsigned)p.split), dim3(64 * WPU), lds, s, a, p)
     if constexpr (NC > kUnitShortNC) {       // half as a full last chunk
-        if (!fused) FQ_UNIT(false, 1, false);
-        else if (dtm == 2) FQ_UNIT(true, 2, false);
+        if (dtm == 2) FQ_UNIT(true, 2, false);
         else FQ_UNIT(true, 4, false);
-    } else if (!fused) {
-        if (half) FQ_UNIT(false, 1, true);
-        else FQ_UNIT(false, 1, false);
     } else if (dtm == 2) {
         if (half) FQ_UNIT(true, 2, true);
         else FQ_UNIT(true, 2, false);
@@ -1574,19 +1571,39 @@ hipError_t launch_unit_nc_w(bool fused, int dtm, bool half, const LisArgs& a, co
         if (half) FQ_UNIT(true, 4, true);
         else FQ_UNIT(true, 4, false);
     }
-#undef FQ_UNIT
     return hipGetLastError();
 }
 
-// wpu: wavefronts per unit, 1 or 2 for rows of up to 4 chunks, else 4.
+// Codes only: one wavefront a workgroup; DTMAX is 1 for dense code rows and 0
+// for rows with padding.
+template <int NC>
+hipError_t launch_unit_codes(bool half, const LisArgs& a, const LisLaunch& p, size_t lds,
+                             hipStream_t s) {
+    constexpr int WPU = 1;
+    if constexpr (NC > kUnitShortNC) {       // always dense
+        FQ_UNIT(false, 1, false);
+    } else if (p.codes_ldw != 0) {
+        if (half) FQ_UNIT(false, 1, true);
+        else FQ_UNIT(false, 1, false);
+    } else {
+        if (half) FQ_UNIT(false, 0, true);
+        else FQ_UNIT(false, 0, false);
+    }
+    return hipGetLastError();
+}
+#undef FQ_UNIT
+
+// wpu: wavefronts per workgroup of the fused head, 1 or 2 for rows of up to 4
+// chunks, else unit_long_waves.
 template <int NC>
 hipError_t launch_unit_nc(bool fused, int dtm, bool half, int wpu, const LisArgs& a,
                           const LisLaunch& p, size_t lds, hipStream_t s) {
+    if (!fused) return launch_unit_codes<NC>(half, a, p, lds, s);
     if constexpr (NC <= 4) {
-        if (wpu == 1) return launch_unit_nc_w<NC, 1>(fused, dtm, half, a, p, lds, s);
-        if (wpu == 2) return launch_unit_nc_w<NC, 2>(fused, dtm, half, a, p, lds, s);
+        if (wpu == 1) return launch_unit_nc_w<NC, 1>(dtm, half, a, p, lds, s);
+        if (wpu == 2) return launch_unit_nc_w<NC, 2>(dtm, half, a, p, lds, s);
     }
-    return launch_unit_nc_w<NC, unit_long_waves(NC)>(fused, dtm, half, a, p, lds, s);
+    return launch_unit_nc_w<NC, unit_long_waves(NC)>(dtm, half, a, p, lds, s);
 }
 
 // Per chunk-count launchers, instantiated in lis_inst_lo.hip (1..10 chunks),

@@ -114,6 +114,21 @@ inline int unit_split(int64_t G, int tiles, int waves, int nc, size_t lds) {
     return (int)best;
 }
 
+// Few tiles, with a partial last chunk: the tile kernel, which stores the codes'
+// bytes from the registers, is up to 15 % faster than gathering the rows in LDS
+// as long as the wavefronts have the SIMDs (nearly) to themselves: nibble codes
+// of up to 288 keys in at most one tile a SIMD (256 units of 49 x 100 4.4 against
+// 5.0 us, 96 of 113 x 113 4.2 and 4.9; with full last chunks 192 of 64 x 128 5.9
+// against 4.8, and units of a few rows 1024 of 1 x 197 8.0 against 7.1), and
+// windows of 49 keys in up to 2.75 (700 of 49 x 49 4.9 against 5.6; 8-bit codes
+// 5.2 and 6.0).  Other byte codes store four times the bytes: never (768 x 197 x
+// 197 62 against 41 us).
+inline bool codes_tile_kernel(int64_t G, int Lq, int nc, int Lk, bool bytes) {
+    const int tiles = (Lq + 15) / 16;
+    const int64_t most = nc <= 2 && tiles >= 4 ? 2816 : bytes ? 0 : kSimds;
+    return nc <= 9 && Lk % 32 != 0 && Lq > 8 && G * tiles > 256 && G * tiles <= most;
+}
+
 inline LisPlan plan_lis(const LisArgs& a) {
     LisPlan s{};
     LisLaunch& p = s.p;
@@ -154,7 +169,7 @@ inline LisPlan plan_lis(const LisArgs& a) {
         u.kb = s.nc * 32;
         u.ld = u.kb + 8;
         u.vt_bytes = s.fused ? u.dpad * u.ld * (int)sizeof(uint16_t) : 0;
-        const int waves = unit_waves(s.nc, tiles16);
+        const int waves = s.fused ? unit_waves(s.nc, tiles16) : 1;
         const size_t wave_lds = (size_t)(s.fused ? unit_lds_dwords(s.dt) : kScreenLds) * sizeof(int32_t);
         size_t lds = (size_t)u.vt_bytes + wave_lds * waves;
         // codes only, dense rows: each wavefront gathers its tile's code rows
@@ -163,18 +178,14 @@ inline LisPlan plan_lis(const LisArgs& a) {
             u.codes_ldw = (16 * row_bytes + 8 + 15) / 16 * 16;
             lds += (size_t)waves * u.codes_ldw;
         }
-        bool single = false;
-        if (s.fused) {
-            u.split = unit_split(a.G, tiles16, waves, s.nc, lds);
-        } else {
-            // As many workgroups per unit as fill the workgroup slots of 256
-            // CUs; one tile a wavefront: the tile kernel.
-            const int64_t slots = 256 * std::max<int64_t>(1, std::min<int64_t>(12 / waves, kMaxLds / lds));
-            const int64_t most = (tiles16 + waves - 1) / waves;
-            u.split = (int)std::max<int64_t>(1, std::min<int64_t>(most, slots / a.G));
-            single = u.split == most && slots >= a.G;
-        }
-        if (!single) {
+        // Codes only: nothing is shared between a unit's tiles, so a workgroup
+        // is one wavefront with one tile (several beyond the grid's limit).
+        // Against workgroups of eight wavefronts for rows of more than 320 keys
+        // and two or four below, several tiles each: 3000 units of 16 x 577
+        // 138 -> 42 us, 300 of 400 x 400 75 -> 46, 144 of 325 x 325 33 -> 22, and
+        // 8-bit codes of 768 x 197 x 197 unchanged.
+        u.split = std::min(s.fused ? unit_split(a.G, tiles16, waves, s.nc, lds) : tiles16, 65535);
+        if (s.fused || !codes_tile_kernel(a.G, a.Lq, s.nc, a.Lk, a.k.top > 15)) {
             s.kernel = LisPlan::kUnit;
             s.p = u;
             s.waves = waves;

@@ -6,7 +6,8 @@ LIMIT = 2 ** 32         # work-items of a launch
 
 
 def threads(p):
-    return p.blocks * 64 * p.waves
+    """Work-items along the launch's first dimension (unit kernel: units)."""
+    return p.blocks // p.split * 64 * p.waves
 
 
 # Few rows a unit and many units (up to about 3000): four wavefronts a unit, of
@@ -55,6 +56,34 @@ def test_fused_short_rows_fill_the_last_pass(plan):
             assert (p.split - 1) * p.waves < tiles
 
 
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("Lq,Lk", [(1, 225), (16, 577), (33, 577), (100, 400), (325, 325), (400, 400),
+                                   (577, 577), (640, 640), (49, 49), (197, 197)])
+def test_stored_codes_have_no_idle_wavefronts(plan, Lq, Lk, bits):
+    """A tile a wavefront, none without one: eight wavefronts a workgroup took
+    3000 units of 16 x 577 from 49 to 138 us, four-tile walks 300 of 400 x 400
+    from 54 to 77."""
+    tiles = -(-Lq // 16)
+    for G in (1, 144, 300, 520, 1000, 3000):
+        p = plan.codes(G, Lq, Lk, bits=bits)
+        if p.kernel == "tile":
+            assert Lk <= 288 and Lk % 32 and Lq > 8
+            assert 256 < G * tiles <= (2816 if Lk <= 64 and tiles >= 4 else 1024 if bits == 4 else 0)
+        else:
+            assert p.kernel == "unit" and p.waves == 1 and p.split == tiles
+            assert p.gathered >= 16 * (Lk if bits > 4 else (Lk + 1) // 2)
+
+
+def test_stored_codes_kernels(plan):
+    """Rows with padding: the unit kernel up to 224 keys; the integer path and
+    longer rows as before."""
+    assert plan.codes(700, 49, 49, pad=1).kernel == "unit"
+    assert plan.codes(700, 49, 49, pad=1).gathered == 0
+    assert plan.codes(700, 49, 225, pad=1).kernel == "tile"
+    assert plan.codes(700, 49, 49, s=2.0 ** -12).kernel == "tile"
+    assert plan.codes(3, 641, 641).kernel == "stream"
+
+
 def test_launches_stay_within_the_grid(plan):
     """Calls of many units stay below 2^32 work-items, and as many units are
     accepted as one 256-thread workgroup a unit allows."""
@@ -63,3 +92,15 @@ def test_launches_stay_within_the_grid(plan):
             assert threads(plan.head(G, 1, Lk, 16)) < LIMIT
     for Lk in (321, 640):
         assert threads(plan.head(2 ** 23 - 1, 1, Lk, 16)) < LIMIT
+    # (units, parts): each dimension of the grid by itself
+    for G, Lq in ((2 ** 23, 1), (2 ** 24 - 1, 16), (2 ** 24, 64), (3, 2 ** 22)):
+        for Lk in (1, 64):
+            for bits in (4, 8):
+                p = plan.codes(G, Lq, Lk, bits=bits)
+                assert p.kernel == "unit" and G * 64 * p.waves < LIMIT and p.split <= 65535
+    # rows of more than 320 keys: eight wavefronts a unit refused 2^23 units
+    for G in (2 ** 23, 2 ** 24 - 1):
+        for Lk in (321, 640):
+            for bits in (4, 8):
+                p = plan.codes(G, 1, Lk, bits=bits)
+                assert G * 64 * p.waves < LIMIT
