@@ -77,8 +77,8 @@ def test_stored_codes_have_no_idle_wavefronts(plan, Lq, Lk, bits):
 def test_stored_codes_kernels(plan):
     """Rows with padding: the unit kernel up to 224 keys; the integer path and
     longer rows as before."""
-    assert plan.codes(700, 49, 49, pad=1).kernel == "unit"
-    assert plan.codes(700, 49, 49, pad=1).gathered == 0
+    assert plan.codes(1500, 49, 49, pad=1).kernel == "unit"
+    assert plan.codes(1500, 49, 49, pad=1).gathered == 0
     assert plan.codes(700, 49, 225, pad=1).kernel == "tile"
     assert plan.codes(700, 49, 49, s=2.0 ** -12).kernel == "tile"
     assert plan.codes(3, 641, 641).kernel == "stream"
