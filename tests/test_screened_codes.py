@@ -156,3 +156,78 @@ def test_rows_on_the_thresholds(fq, orc, G, Lq, Lk, d, n):
     k = torch.zeros((G, Lk, 32), dtype=torch.int8, device="cuda")
     got = fq.lis_attention_qk(q, k, dv, s, exp_n=n, zp_v=5, bias=dl).cpu().numpy()
     assert np.array_equal(got, ref)
+
+
+def _exact_tie_logits(rng, G, Lq, Lk, d, top):
+    """Rows of logits -z d, z <= 20, whose I-Exp values are the maximum's times
+    2^-z, with 2S = c_k e for a key e (c_1 = 3, c_k = 3 2^(k-1) - 1, k <= top):
+    the sum as powers of two, split until there are Lk of them.  In one row of
+    three a key of the smallest value is moved by up to two logits."""
+    n = 20
+    out = np.empty((G, Lq, Lk), dtype=np.int32)
+    for row in out.reshape(-1, Lk):
+        while True:
+            k = int(rng.integers(1, min(top, 12) + 1))
+            zj = 0 if k == 1 else int(rng.integers(max(k - 4, 0), k))
+            M = 3 << (n - 1) if k == 1 else (3 * 2 ** (k - 1) - 1) << (n - zj - 1)
+            z = [0] if zj == 0 else [0, zj]
+            rest = M - sum(1 << (n - a) for a in z)
+            if rest < 0:
+                continue
+            extra = [0] * (rest >> n) + [n - b for b in range(n) if rest >> b & 1]
+            if len(z) + len(extra) <= Lk:
+                break
+        while len(z) + len(extra) < Lk:
+            open_ = [i for i, a in enumerate(extra) if a < n]
+            i = open_[int(rng.integers(len(open_)))]
+            extra[i] += 1
+            extra.append(extra[i])
+        v = -np.array(z + extra, dtype=np.int64) * d
+        if rng.integers(3) == 0:
+            v[np.argmin(v)] += int(rng.integers(-2, 3))
+        row[:] = rng.permutation(v) + int(rng.integers(-50, 50))
+    return out
+
+
+def _undecided_rows(orc, lg, s, n, top):
+    """Rows with a decision that the screen leaves open."""
+    k = orc.iexp_constants(s, n)
+    u, inv = np.unique(lg.max(-1, keepdims=True).astype(np.int64) - lg, return_inverse=True)
+    e = np.array([orc.iexp(-int(x), k)[0] for x in u], dtype=np.float64)[inv].reshape(lg.shape)
+    e *= 2.0 ** -n
+    count = 0
+    for row in e.reshape(-1, lg.shape[-1]):
+        _, und, tau = _screen(row.astype(np.float32), np.full(row.shape, row.sum()), top)
+        count += bool(und.any() or abs(tau[0] - row.max()) < row.max() * 2.0 ** -18)
+    return count
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("s,bits", [(2.0 ** -8, 4), (2.0 ** -8, 3), (2.0 ** -10, 4), (2.0 ** -10, 3),
+                                    (0.05, 4)])
+@pytest.mark.parametrize("Lk", [12, 16, 33, 96, 120, 150, 176, 197, 224, 230, 288, 400, 448, 461, 577, 640])
+def test_rows_on_exact_thresholds(fq, orc, plan, s, bits, Lk):
+    """Every row on a threshold or beside one, at scales with the I-Exp pre-shift
+    (above 1.3e-3) and without, codes cut at 7, 15 and 255, rows of each kernel,
+    Q and K of both widths."""
+    import torch
+    G, Lq, d = 5, 24, (64, 32)[Lk % 2]
+    print("CASE exact thresholds", s, bits, Lk, flush=True)
+    rng = np.random.default_rng(Lk + bits)
+    lg = _exact_tie_logits(rng, G, Lq, Lk, -orc.iexp_constants(s, 20).q_ln2, 2 ** bits - 1)
+    assert _undecided_rows(orc, lg, s, 20, 2 ** bits - 1) > G * Lq // 2
+    assert plan.head(G, Lq, Lk, d, s=s, bits=bits).kernel == "unit"
+    v = rng.integers(-128, 128, size=(G, Lk, d)).astype(np.int8)
+    dl, dv = torch.from_numpy(lg).cuda(), torch.from_numpy(v).cuda()
+    ref = orc.lis_attention_head(lg, v, s, bits=bits, zp_v=5)
+    got = fq.lis_attention_head(dl, dv, s, bits=bits, zp_v=5).cpu().numpy()
+    assert np.array_equal(got, ref)
+    for b in (bits, 8):
+        assert plan.codes(G, Lq, Lk, s=s, bits=b).kernel == "unit"
+        got = fq.lis_softmax_log4(dl, s, bits=b).cpu().numpy()
+        assert np.array_equal(got, orc.lis_softmax_log4(lg, s, bits=b))
+    for dk in (32, 64):
+        q = torch.zeros((G, Lq, dk), dtype=torch.int8, device="cuda")
+        k = torch.zeros((G, Lk, dk), dtype=torch.int8, device="cuda")
+        got = fq.lis_attention_qk(q, k, dv, s, bits=bits, zp_v=5, bias=dl).cpu().numpy()
+        assert np.array_equal(got, ref)
