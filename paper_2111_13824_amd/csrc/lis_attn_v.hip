@@ -207,10 +207,17 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
     constexpr int NW = BYTES ? 5 : 3;
     extern __shared__ __attribute__((aligned(16))) uint8_t vt[];   // [16 DT][ldv] int8
     __shared__ int s_floor;
-    // part of unit g: tiles 4 part + wave, then every 4 m.split
-    const int64_t lb = xcd_remap(blockIdx.x, a.G * m.split);
-    const int64_t g = lb / m.split;
-    const int first = 4 * (int)(lb - g * m.split);
+    // part of unit g: tiles 4 part + wave, then every 4 m.split (split is 1 or
+    // G m.split <= 512, see launch_any; a 64-bit division for every launch took
+    // 0.1 to 0.2 us, 3 to 6 % of one of 16 x 16)
+    int64_t g = xcd_remap(blockIdx.x, a.G * m.split);
+    int first = 0;
+    if (m.split > 1) {
+        const int lb = (int)g;
+        const int u = lb / m.split;
+        g = u;
+        first = 4 * (lb - u * m.split);
+    }
     const int step = 4 * m.split;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -230,7 +237,8 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
 
     // The wavefront's steps: its tiles, each in nks steps of 64 keys; (pt, pks) is the step whose codes are requested next.  The first
     // window is requested before V^T is staged.
-    const int my_tiles = m.ntiles > first + wave ? (m.ntiles - first - wave + step - 1) / step : 0;
+    const int over = m.ntiles - first - wave + step - 1;
+    const int my_tiles = over < step ? 0 : m.split > 1 ? over / step : over >> 2;
     const int nsteps = my_tiles * nks;
     auto row_of = [&](int t) {
         return t < m.ntiles ? min(16 * t + r, a.Lq - 1) * a.ld_codes + mis : -1;
