@@ -98,7 +98,26 @@ inline int unit_split(int64_t G, int tiles, int waves, int nc, size_t lds) {
     // workgroups per unit that leave a wavefront t tiles
     auto split_of = [&](int64_t t) { return (tiles + waves * t - 1) / (waves * t); };
     const int64_t fill = std::max<int64_t>(1, std::min<int64_t>(most, slots / G));
-    if (fill > 1 || nc < 8 || nc > 9) return (int)split_of((tiles + waves * fill - 1) / (waves * fill));
+    const int64_t even = split_of((tiles + waves * fill - 1) / (waves * fill));
+    if (fill > 1 && (nc == 9 || nc == 10)) {
+        // Rows of 257 to 320 keys, divided: the CUs that get a workgroup more
+        // than the others end last, so a unit's load is its workgroups a CU,
+        // rounded up, times the tiles a wavefront and the staging (0.6 of a
+        // tile), and 1.3 times that where a SIMD has one wavefront and nothing
+        // to run while it waits.  Over 100 to 256 units of 257 to 320 keys this
+        // is within 8 % of the best division (200 units of 288 x 288 29.1 us by
+        // `even`, 27.7 by this; 180 of 300 x 300 with a bias 29.9 and 26.1).
+        auto cost = [&](int64_t split) {
+            const int64_t load = (G * split + 255) / 256;
+            return (double)load * ((double)((tiles + waves * split - 1) / (waves * split)) + 0.6) *
+                   (load == 1 ? 1.3 : 1.0);
+        };
+        int64_t best = even;
+        for (int64_t t = 1; t <= most; ++t)
+            if (cost(split_of(t)) < cost(best)) best = split_of(t);
+        return (int)best;
+    }
+    if (fill > 1 || nc < 8 || nc > 9) return (int)even;
     // Rows of 225 to 288 keys, more units than half the slots: the SIMDs that
     // get a wavefront more than the others end last, so the load of one is its
     // wavefronts, rounded up, times the tiles each walks and the staging (0.3 of

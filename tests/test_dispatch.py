@@ -56,6 +56,19 @@ def test_fused_short_rows_fill_the_last_pass(plan):
             assert (p.split - 1) * p.waves < tiles
 
 
+def test_fused_rows_of_320_keys_are_divided_evenly(plan):
+    """Rows of 257 to 320 keys, fewer units than CUs: as many workgroups as fill
+    the slots could leave some CUs with one more than the others (200 units of 288
+    x 288 29.1 us with two a unit, 27.7 with five; 180 of 300 x 300 with a bias
+    29.9 and 26.1).  More units, and two workgroups a unit are the better ones
+    again (240 of 257 x 257 24.3 us, 28.1 with five)."""
+    assert plan.head(200, 288, 288, 64).split == 5
+    assert plan.head(180, 300, 300, 32, Hb=3).split == 5
+    assert plan.head(160, 257, 257, 64).split == 3
+    assert plan.head(240, 257, 257, 64).split == 2
+    assert plan.head(60, 320, 320, 64).split == 5
+
+
 @pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("Lq,Lk", [(1, 225), (16, 577), (33, 577), (100, 400), (325, 325), (400, 400),
                                    (577, 577), (640, 640), (49, 49), (197, 197)])
