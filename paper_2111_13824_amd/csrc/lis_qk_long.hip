@@ -54,8 +54,8 @@ __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, Qk
     uint16_t* vt = reinterpret_cast<uint16_t*>(smem);
     int8_t* kst = reinterpret_cast<int8_t*>(smem + p.vt_bytes);
     int32_t* ck = reinterpret_cast<int32_t*>(smem + p.vt_bytes + kp * DK);
-    const int part = (int)(blockIdx.x / (unsigned)a.G);     // as lis_qk_kernel
-    const int64_t g = blockIdx.x - (unsigned)part * (unsigned)a.G;
+    const int part = (int)blockIdx.y;     // as lis_qk_kernel
+    const int64_t g = blockIdx.x;
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int r = lane & 15;
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kQkLongBlock) void lis_qk_long_kernel(LisArgs a, Qk
 
 hipError_t launch_qk_long_int(int dk, int dtm, const LisArgs& a, const QkArgs& qa,
                               const LisLaunch& p, size_t lds, hipStream_t stream) {
-    const dim3 grid((unsigned)(a.G * p.split)), block(kQkLongBlock);
+    const dim3 grid((unsigned)a.G, (unsigned)p.split), block(kQkLongBlock);
 #define FQ_QKL(DT, DK)                                                                            \
     do {                                                                                          \
         if (a.bias)                                                                               \
