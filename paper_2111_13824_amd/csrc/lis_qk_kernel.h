@@ -279,6 +279,12 @@ __global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_
     constexpr int NTHR = 64 * WAVES;
     constexpr int NT = HALF ? 4 : 8;
     constexpr int KP = 32 * NC;                 // staged keys (zero past Lk)
+    // Integer path: a group of chunks at a time, and the next queries' bytes
+    // requested at the tile's end.  Not rows of three and four chunks, which then
+    // take a few registers more than five and four wavefronts a SIMD leave them
+    // (1000 units of 100 x 100 at 2^-12 19.4 us, as it is 17.4); of two chunks, 6144
+    // units of 49 x 49 39.3 us without and 37.4 with.
+    constexpr bool kTight = !FP && NC != 3 && NC != 4;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint16_t* vt = reinterpret_cast<uint16_t*>(smem);
     int8_t* kst = reinterpret_cast<int8_t*>(smem + p.vt_bytes);
@@ -339,12 +345,12 @@ __global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_
                     qk_chunk<DK, HALF, BIAS>(lg[c], kst, ck, qb, qb8, bias[c0 / kQkGroup % 2][u], c, r, kg,
                                              a.Lk, c == NC - 1);
             }
-            if (NC > kQkRegsNC || !FP) __builtin_amdgcn_sched_barrier(0);
+            if (NC > kQkRegsNC || kTight) __builtin_amdgcn_sched_barrier(0);
         }
         // the next tile's query bytes, in flight during the rest of this tile
-        // (integer path: requested at its end, where its registers are free)
+        // (kTight: requested at its end, where its registers are free)
         const int nt = min(16 * (tile + step < p.ntiles ? tile + step : tile) + r, a.Lq - 1);
-        if (FP) qk_load_q<DK>(q_base, nt, kg, qb, qb8);
+        if (!kTight) qk_load_q<DK>(q_base, nt, kg, qb, qb8);
         f32x4 acc[DTMAX];
 #pragma unroll
         for (int dt = 0; dt < DTMAX; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -387,7 +393,7 @@ __global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (!FP) qk_load_q<DK>(q_base, nt, kg, qb, qb8);
+        if (kTight) qk_load_q<DK>(q_base, nt, kg, qb, qb8);
         store_out_t<DTMAX>(acc, a, g, i0, r, kg, p.out_vec);
     }
 }

@@ -27,8 +27,9 @@ def _code_objects(data):
 
 
 @pytest.fixture(scope="module")
-def scratch(tmp_path_factory):
-    """Bytes of scratch a lane of every kernel, by demangled name."""
+def resources(tmp_path_factory):
+    """(bytes of scratch a lane, vector registers) of every kernel, by demangled
+    name."""
     from paper_2111_13824_amd import binding
     if not os.path.exists(binding.LIB_PATH):
         pytest.fail("libfqvit.so is not built")
@@ -44,13 +45,19 @@ def scratch(tmp_path_factory):
         for block in re.split(r"\n  - (?=\.)", text)[1:]:
             name = re.search(r"^\s*\.name:\s+(_Z\S+)$", block, re.M)
             size = re.search(r"\.private_segment_fixed_size:\s+(\d+)", block)
-            if name and size:
+            regs = re.search(r"\.vgpr_count:\s+(\d+)", block)
+            if name and size and regs:
                 names.append(name.group(1))
-                sizes.append(int(size.group(1)))
+                sizes.append((int(size.group(1)), int(regs.group(1))))
     plain = subprocess.run(["c++filt"], input="\n".join(names), capture_output=True, text=True,
                            check=True).stdout.split("\n")
     return {n.split("(fqvit")[0].replace("void ", "").replace("fqvit::lis::", ""): s
             for n, s in zip(plain, sizes)}
+
+
+@pytest.fixture(scope="module")
+def scratch(resources):
+    return {n: s for n, (s, _) in resources.items()}
 
 
 def _spilling(scratch, kernel):
@@ -79,6 +86,19 @@ def test_qk_integer_rows_of_197_keys_hold_their_state(scratch):
         nc, half, bias = int(args[0]), args[2] == "true", args[6] == "true"
         limit = 0 if nc < 7 or (half and not bias) else 80
         assert s <= limit, (n, s)
+
+
+def test_qk_integer_rows_keep_their_wavefronts(resources):
+    """Integer path, rows of three and four chunks: at most the 96 and 128
+    registers that five and four wavefronts a SIMD leave each.  With 129, 1000
+    units of 100 x 100 took 19.4 us instead of 17.4."""
+    seen = 0
+    for n, (_, regs) in resources.items():
+        args = [x.strip(" >") for x in n.split("<")[-1].split(",")]
+        if n.startswith("lis_qk_kernel<") and args[3] == "false" and args[0] in ("3", "4"):
+            assert regs <= (96 if args[0] == "3" else 128), (n, regs)
+            seen += 1
+    assert seen
 
 
 def test_unit_kernels_hold_their_rows(scratch):
