@@ -260,7 +260,10 @@ __device__ __forceinline__ void qk_fix_chunks(f32x4 (&acc)[DTMAX], uint32_t todo
 // forming them again for the maximum, the sum and the codes: 256 units of 577 x
 // 577, dk = d = 64, 148 -> 89 us.
 constexpr int qk_waves(int NC) { return NC <= 10 ? 4 : 8; }
-constexpr int qk_waves_per_simd(int NC) { return NC <= 8 ? 3 : 2; }
+constexpr int qk_waves_per_simd(int NC, bool FP) {
+    if (!FP && NC == 4) return 4;       // some forms take 131 to 134 registers by themselves
+    return NC <= 8 ? 3 : 2;
+}
 constexpr int kQkGroup = 3;     // chunks whose K reads and bias are in flight together
 
 // Workgroup (g, part) does part `part` of unit g: the unit's tiles are dealt to
@@ -273,7 +276,7 @@ constexpr int kQkGroup = 3;     // chunks whose K reads and bias are in flight t
 // loop).  256 units of 577 x 577, dk = d = 64: 82 -> 68 us, with a bias 142 ->
 // 90 us.
 template <int NC, int DTMAX, bool HALF, bool FP, int DK, bool P0, bool BIAS>
-__global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC)) void lis_qk_kernel(
+__global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC, FP)) void lis_qk_kernel(
     LisArgs a, QkArgs qa, LisLaunch p) {
     constexpr int WAVES = qk_waves(NC);
     constexpr int NTHR = 64 * WAVES;
