@@ -14,8 +14,9 @@ LIB = os.path.join(HERE, "libfqvit.so")
 SOURCES = ["ptf_layernorm.hip", "lis_attention.hip", "lis_inst_lo.hip", "lis_inst_hi.hip",
            "lis_inst_unit.hip", "ptf_quant.hip", "lis_qk.hip", "lis_qk_dk32.hip",
            "lis_qk_dk64.hip", "lis_unit_long.hip", "lis_unit_long.hip:FQ_UNIT_HI",
-           "lis_qk_long.hip", "lis_qk_long_dk32.hip", "lis_qk_long_dk64.hip",
-           "lis_qk_long_dk32.hip:FQ_QK_HI", "lis_qk_long_dk64.hip:FQ_QK_HI", "lis_attn_v.hip",
+           "lis_qk_long.hip", "lis_qk_long_float.hip:FQ_QK32_LO",
+           "lis_qk_long_float.hip:FQ_QK32_HI", "lis_qk_long_float.hip:FQ_QK64_LO",
+           "lis_qk_long_float.hip:FQ_QK64_HI", "lis_attn_v.hip",
            "fqvit_abi.cpp"]     # "file:MACRO": compiled with -DMACRO
 OBJDIR = os.path.join(HERE, "_build")
 

@@ -23,8 +23,9 @@
 // on the vector ALUs (from the V^T staged for it).
 //
 // A workgroup of four wavefronts per attention unit (several where the units
-// alone would leave CUs idle): V^T of the unit is staged in LDS as int8 (keys padded to a multiple of 64 with zeros); each
-// wavefront walks the unit's 16-row tiles.  Lane (r, kq) takes query row
+// alone would leave CUs idle): V^T of the unit is staged in LDS as int8 (keys
+// padded to a multiple of 64 with zeros); each wavefront walks the unit's 16-row
+// tiles.  Lane (r, kq) takes query row
 // i0 + r and keys 64 ks + 16 kq .. + 15 of each 64-key step, its code bytes
 // straight from memory as aligned dwords and funnel shifts:
 //   * nibble codes: eight bytes, the nibbles spread into bytes (keys
@@ -35,7 +36,8 @@
 //     (s = 7 k + e) of each as a byte, packed, and per range the bytes whose k
 //     it is, selected by one byte permute (25 instructions for four keys; a
 //     64-bit 2^(8 k + e) per key and a byte transpose took about 55).  With it
-//     and the joined sums (av_join64): ViT-B/16, 8-bit codes, 54 -> 35 us.
+//     and the joined sums (av_join64): 768 x 197 x 197 with d = 64, 8-bit codes,
+//     timed over a loop of calls, 51.6 -> 36.2 us.
 // The B operand of the MFMA is P_k^T (keys x rows), the A operand V^T
 // (columns x keys), so the output lane (r, kq) holds columns 16 ct + 4 kq .. + 3
 // of row i0 + r.  The codes of the next four (nibble codes) or two (byte
@@ -409,7 +411,11 @@ __global__ __launch_bounds__(256, 2) void attn_v_mfma_kernel(AvK a, AvMfma m) {
                             for (int t = 0; t < 4; ++t) res[t] = av_join64<NS>(acc[ct], t) - zterm;
                             const int c0 = 16 * ct + 4 * kq;
                             if (m.vec_out && c0 + 3 < d) {
-                                // streaming: the output is not read again here
+                                // streaming: the output is not read again here.
+                                // The 16-byte halves of a lane's 32 bytes go out
+                                // apart, and 3 to 6 % more than the output is
+                                // written; with the default policy 768 x 197 x
+                                // 197 takes 37.7 us, so 35.9.
                                 __builtin_nontemporal_store(av_u64x2{res[0], res[1]},
                                                             reinterpret_cast<av_u64x2*>(orow + c0));
                                 __builtin_nontemporal_store(av_u64x2{res[2], res[3]},

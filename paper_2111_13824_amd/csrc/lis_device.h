@@ -390,33 +390,23 @@ __device__ __forceinline__ int lis_code(uint32_t qL, uint32_t z, const RowSum& r
 // Float path
 // ---------------------------------------------------------------------------
 
-// I-Exp of one key for the float path, from its clamped input u = max - v:
-// e = qL 2^(n - z) as a binary32 value (exact: qL < 2^24).  z, q_p + q_b and qL
-// come from the 24-bit integer
-// steps of iexp_qL (magic division by a multiply-high, two 24-bit
-// multiply-adds), which cost less than binary32 arithmetic; the host accepts
-// only scales for which those steps are exact.  k.magic and the shifted u are
-// below 2^24, so the product maps to one v_mul_hi_u32_u24.
-// P0: the pre-shift is known to be 0 (|q_ln2| > 256, i.e. s below about
-// 2.7e-3), which saves the shift of every key.
-template <bool P0 = false>
-__device__ __forceinline__ float iexp_fu(uint32_t u, const LisConsts& k) {
-    const uint32_t us = P0 ? u : (u << k.pre);
+// I-Exp of one key for the float path, a logit v of a row with maximum mx: u =
+// mx - v clamped at n |q_ln2|, e = qL 2^(n - z) as a binary32 value (exact: qL <
+// 2^24).  z, q_p + q_b and qL come from the 24-bit integer steps of iexp_qL
+// (magic division by a multiply-high, two 24-bit multiply-adds), which cost less
+// than binary32 arithmetic; the host accepts only scales for which those steps
+// are exact.  k.magic and the shifted u are below 2^24, so the product maps to
+// one v_mul_hi_u32_u24.
+__device__ __forceinline__ float iexp_f(int v, int mx, const LisConsts& k) {
+    const uint32_t u = min((uint32_t)mx - (uint32_t)v, k.u_max);
     const uint32_t z =
-        (uint32_t)(((uint64_t)(us & 0xFFFFFFu) * (uint64_t)(k.magic & 0xFFFFFFu)) >> 32);
+        (uint32_t)(((uint64_t)((u << k.pre) & 0xFFFFFFu) * (uint64_t)(k.magic & 0xFFFFFFu)) >> 32);
     // q_p + q_b = z d + (q_b - u); written out because the compiler would
     // otherwise select a 64-bit multiply-add
     uint32_t w;
     asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(w) : "v"(z), "s"(k.d_ln2), "v"(k.qb - u));
     const uint32_t qL = __umul24(w, w) + k.qc;
     return __builtin_ldexpf((float)qL, k.n - (int)z);
-}
-
-// The same for a logit v of a row with maximum mx: u = mx - v clamped at
-// n |q_ln2|.
-template <bool P0 = false>
-__device__ __forceinline__ float iexp_f(int v, int mx, const LisConsts& k) {
-    return iexp_fu<P0>(min((uint32_t)mx - (uint32_t)v, k.u_max), k);
 }
 
 // Code of one key on the float path, from e (its binary32 bit pattern) and the
@@ -627,7 +617,7 @@ __device__ __forceinline__ int tile_max(const int (&lg)[NC][8]) {
     return row4_max(mx);
 }
 
-template <int NC, bool FP, int NT, bool P0 = false>
+template <int NC, bool FP, int NT>
 __device__ __forceinline__ RowState tile_iexp(int (&lg)[NC][8], uint32_t (&zb)[NC][2],
                                               const LisConsts& k) {
     const int mx = tile_max<NC>(lg);
@@ -642,7 +632,7 @@ __device__ __forceinline__ RowState tile_iexp(int (&lg)[NC][8], uint32_t (&zb)[N
 #pragma unroll
             for (int t = 0; t < (c < NC - 1 ? 8 : NT); ++t) {
                 const int v = lg[c][t];
-                float e = iexp_f<P0>(v, mx, k);
+                float e = iexp_f(v, mx, k);
                 if (c == NC - 1) e = v != INT_MIN ? e : 0.0f;
                 part[t & 3] += (double)e;
                 lg[c][t] = __float_as_int(e);
@@ -1290,8 +1280,8 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
         else store_out<DTMAX>(acc, a, g, i0, r, kg);
         return;
     }
-    // Codes only (screened: ViT-B/16 50.2 -> 46.2 us with 8-bit codes; 60 units
-    // of 577 x 577 24 us less than in the tile kernel).  ot: the code rows'
+    // Codes only, screened (8-bit codes of 768 x 197 x 197, timed over a loop of
+    // calls: 45.2 us in binary64 with several tiles a wavefront, 31.9 so).  ot: the code rows'
     // region, then an undecided chunk's.
     double S;
     const ScreenRow st = tile_iexp_screen<NC, NT, true, false, true>(cur, k, S);

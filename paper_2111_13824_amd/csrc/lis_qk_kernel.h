@@ -385,7 +385,7 @@ __global__ __launch_bounds__(64 * qk_waves(NC), qk_waves_per_simd(NC, FP)) void 
             }
         } else {
             uint32_t zb[NC][2];
-            const RowState st = tile_iexp<NC, FP, NT, P0>(lg, zb, k);
+            const RowState st = tile_iexp<NC, FP, NT>(lg, zb, k);
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const u32x4 pb = chunk_pbits<NC, FP, NT>(lg, zb, st, k, c);
@@ -453,8 +453,8 @@ hipError_t launch_qk_dk(int nc, int dtm, bool half, int fp, const LisArgs& a, co
 
 hipError_t launch_qk_dk32(int nc, int dtm, bool half, int fp, const LisArgs& a, const QkArgs& qa,
                           const LisLaunch& p, size_t lds, hipStream_t stream);
-// Rows of 8 to 20 chunks: the float path (lis_qk_long_dk32.hip,
-// lis_qk_long_dk64.hip, 8..14 and 15..20 chunks), and the integer path, which
+// Rows of 8 to 20 chunks: the float path (lis_qk_long_float.hip,
+// 8..14 and 15..20 chunks), and the integer path, which
 // takes the three passes of qk_tile_passes (lis_qk_long.hip).
 hipError_t launch_qk_long32_lo(int nc, int dtm, int fp, const LisArgs& a, const QkArgs& qa,
                                const LisLaunch& p, size_t lds, hipStream_t stream);

@@ -228,8 +228,8 @@ def test_lis_codes_bits(fq, orc, bits):
 
 
 @pytest.mark.parametrize("G,Lq,Lk,bits,sigma", [
-    (1024, 17, 197, 8, 9.0),     # unit kernel (enough units for it)
-    (6, 40, 300, 6, 6.0),        # tile kernel
+    (1024, 17, 197, 8, 9.0),     # unit kernel
+    (6, 40, 300, 6, 6.0),        # tile kernel (padded rows of more than 224 keys)
     (2, 9, 900, 5, 9.0),         # stream kernel (long rows)
     (1024, 16, 49, 8, 9.0),
 ])
@@ -458,9 +458,9 @@ def test_attention_888_full_vit_base(fq, orc):
     assert np.array_equal(out, np.concatenate([p[1] for p in parts]))
 
 
-# (2, 40, 288, 64) and (2, 33, 270, 32): the longest rows of the fused tile
-# kernels (9 chunks of 32 keys); (2, 40, 290, 64): the shortest that takes the
-# stream kernel, with (2, 40, 350, 64), (2, 33, 384, 32) and (2, 40, 400, 64)
+# Rows of up to 640 keys with d <= 64 take the unit kernel, longer rows and
+# larger d the stream kernel; 270 to 400 keys: one to four wavefronts' worth of
+# tiles in rows of 9 to 13 chunks.
 HEAD_SHAPES = [(3, 5, 1, 64), (2, 17, 33, 16), (3, 64, 197, 64), (2, 70, 197, 64), (1, 65, 577, 64),
                (12, 49, 49, 32), (2, 3, 640, 64), (1, 3, 700, 64), (1, 2, 4096, 32), (2, 20, 96, 100),
                (2, 33, 65, 256), (2, 19, 129, 1), (2, 40, 288, 64), (2, 33, 270, 32),
@@ -477,8 +477,8 @@ def test_head_shapes(fq, orc, G, Lq, Lk, d):
     assert np.array_equal(got, ref)
 
 
-# Long rows (10 to 20 chunks of 32 keys) take the long-row kernel: logits read
-# once, I-Exp from an LDS table.
+# Long rows (10 to 20 chunks of 32 keys), which the unit kernel holds in
+# registers one tile at a time.
 LONG_SHAPES = [(3, 70, 577, 64, 0), (2, 33, 289, 32, 0), (2, 17, 640, 64, 2), (3, 50, 400, 17, 3),
                (2, 40, 313, 48, 2), (4, 16, 336, 64, 0), (2, 1, 600, 8, 0)]
 
@@ -494,9 +494,8 @@ def test_head_long_rows(fq, orc, G, Lq, Lk, d, Hb):
 
 
 def test_head_long_rows_wide_span(fq, orc):
-    """Rows whose logits span more than 2^15 units (a tile holding one of them
-    is computed from the logits again), beside ordinary tiles, in units whose
-    first chunk does not hold the row maximum."""
+    """Rows whose logits span more than 2^15 units, beside ordinary tiles, in
+    units whose first chunk does not hold the row maximum."""
     say("head long wide span")
     a = W.attn_inputs(3, 100, 577, 64, seed=31, sigma=(3.0,), v_lo=-128, v_hi=127)
     lg = a["logits"].copy()
@@ -510,18 +509,17 @@ def test_head_long_rows_wide_span(fq, orc):
 
 @pytest.mark.parametrize("n", [23, 25])
 def test_head_long_rows_clamp_depth(fq, orc, n):
-    """n = 23: an I-Exp table of 16331 entries (65 KB of LDS beside V^T); n = 25:
-    beyond the table's 16-bit offsets, the stream kernel."""
+    """Clamp depths above the default (row sums of up to 2^49 and 2^51)."""
     say("head long depth", n)
     a = W.attn_inputs(2, 40, 577, 64, seed=n, sigma=(6.0,))
     got = host(fq.lis_attention_head(dev(a["logits"]), dev(a["v"]), S, exp_n=n))
     assert np.array_equal(got, orc.lis_attention_head(a["logits"], a["v"], S, exp_n=n))
 
 
-# Shapes with enough units that the launch takes the one-workgroup-per-unit
-# kernel (G * min(4, ceil(Lq / 16)) >= 2048): half and full last chunks, waves
-# with several 16-row tiles, head dimensions that take the byte-wise V loads
-# (d % 16 != 0) and the scalar output stores (d % 4 != 0).
+# The unit kernel at throughput sizes: half and full last chunks, head dimensions
+# that take the byte-wise V loads (d % 16 != 0) and the scalar output stores
+# (d % 4 != 0).  Its instances one by one, and wavefronts that walk several
+# tiles: test_unit_instances_gpu.py.
 UNIT_SHAPES = [(1024, 17, 16, 64), (1024, 17, 17, 64), (1024, 20, 100, 64), (512, 70, 197, 64),
                (600, 49, 49, 32), (512, 65, 224, 64), (700, 33, 120, 48), (700, 33, 120, 20),
                (2048, 2, 40, 17), (2048, 1, 5, 64),

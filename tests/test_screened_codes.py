@@ -139,7 +139,9 @@ SHAPES = [(1024, 17, 5, 32), (700, 33, 49, 32), (520, 49, 130, 64), (512, 70, 19
 @pytest.mark.parametrize("n", [20, 4])
 def test_rows_on_the_thresholds(fq, orc, G, Lq, Lk, d, n):
     """The fused head, the stored codes (4 and 8 bits) and the attention from Q
-    and K (Q zero, so that its logits are the bias) on such rows."""
+    and K (Q zero, so that its logits are the bias) on such rows (rows of more
+    than a few keys come near the thresholds only: the keys far below add up;
+    test_rows_on_exact_thresholds has them on the thresholds)."""
     import torch
     print("CASE screened ties", G, Lq, Lk, d, n, flush=True)
     rng = np.random.default_rng(G + Lk + n)
