@@ -509,7 +509,8 @@ def test_head_long_rows_wide_span(fq, orc):
 
 @pytest.mark.parametrize("n", [23, 25])
 def test_head_long_rows_clamp_depth(fq, orc, n):
-    """Clamp depths above the default (row sums of up to 2^49 and 2^51)."""
+    """Clamp depths beyond the float path's bound on the row sum ((2 Lk + 1)(q_b^2
+    + q_c) 2^n < 2^52): the integer path, in the stream kernel."""
     say("head long depth", n)
     a = W.attn_inputs(2, 40, 577, 64, seed=n, sigma=(6.0,))
     got = host(fq.lis_attention_head(dev(a["logits"]), dev(a["v"]), S, exp_n=n))
