@@ -104,7 +104,7 @@ inline int unit_split(int64_t G, int tiles, int waves, int nc, size_t lds) {
         // than the others end last, so a unit's load is its workgroups a CU,
         // rounded up, times the tiles a wavefront and the staging (0.6 of a
         // tile), and 1.3 times that where a SIMD has one wavefront and nothing
-        // to run while it waits.  Over 100 to 256 units of 257 to 320 keys this
+        // to run while it waits.  Over 100 to 350 units of 257 to 320 keys this
         // is within 8 % of the best division (200 units of 288 x 288 29.1 us by
         // `even`, 27.7 by this; 180 of 300 x 300 with a bias 29.9 and 26.1).
         auto cost = [&](int64_t split) {

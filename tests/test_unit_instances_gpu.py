@@ -69,7 +69,7 @@ def test_fused_instances(fq, orc, plan, nc):
 # row among them (the one-row path of rows of up to two chunks)
 WALKS = [(1600, 49, 20, 64, 0), (1600, 64, 70, 32, 4), (3100, 33, 40, 17, 0), (800, 81, 100, 48, 5),
          (300, 305, 33, 64, 0), (300, 300, 64, 32, 3), (260, 209, 180, 64, 2), (300, 150, 224, 64, 0),
-         (400, 81, 257, 64, 0), (260, 145, 320, 32, 0), (130, 145, 370, 64, 2), (100, 300, 430, 64, 0),
+         (400, 81, 257, 64, 0), (300, 97, 320, 64, 0), (130, 145, 370, 64, 2), (100, 300, 430, 64, 0),
          (130, 145, 500, 32, 0), (130, 145, 640, 64, 2)]
 
 
