@@ -513,19 +513,21 @@ __device__ __forceinline__ float third_floor_f32(double S2) {
 //     T - 1 - m (an exact power of two, where the quotient of the true B would
 //     count one too many, computes just below it and is caught).  The
 //     subtraction saturates at 0: min(m, top).
-//   * [2S < 3e]: only the row maximum (u = 0) can satisfy it, when e0 > X / 2.
-//     Y is then Xs, whose quotient by e0 lies in [4/3, 2) 2^-T: one code less.
-//     The comparison errs only towards the larger code, and a row whose X / 2
-//     is within 2^-18 of e0 counts as undecided.
+//   * [2S < 3e]: only a row's single maximum (u = 0) can satisfy it, since any
+//     other e_j has S >= e0 + e_j >= 2 e_j; and then e_j <= S - e0 < e0 / 2.  It
+//     is decided once a row from the exact sum (tau = 3/4 e0, or no bound): Y of
+//     the maximum is then Xs, whose quotient by e0 lies in [4/3, 2) 2^-T, one
+//     code less.  Kernels that sum in binary32 first decide from S', and take the
+//     exact sum where S' is within 2^-21 of 3/2 e0.  (Such rows had every chunk
+//     undecided before: one in 12 units of 577 x 577, 8-bit codes, 29.1 -> 15.9 us.)
 // ---------------------------------------------------------------------------
 constexpr uint32_t kScreenZone = 16;      // residues of the last 16 of 2^23 are undecided
 
 struct ScreenRow {
     float Xs;       // 4 S / 3 2^-T, biased up
-    float tau;      // 2 S / 3 (scaled by 2^-n), biased up by more than its error
+    float tau;      // 3/4 e0 where 2 S < 3 e0, else infinity
     float c;        // 2 / 3 2^-T, rounded up (uniform)
     int32_t mc;     // screen_c of the row
-    uint64_t tie;   // lanes whose row has X / 2 too close to e0 to tell (uniform)
 };
 
 // T - 1, where T is the power the quotient is scaled by: top, but at most 62
@@ -570,14 +572,20 @@ __device__ __forceinline__ uint32_t screen_iexp(int v, int32_t c, const LisConst
     return ((uint32_t)nz << 23) + __float_as_uint(qL);
 }
 
+// The I-Exp of a row's maximum, 2^-n scaled.
+__device__ __forceinline__ float screen_e0(const LisConsts& k) { return (float)(k.qb * k.qb + k.qc); }
+
+__device__ __forceinline__ float screen_tau(double S, const LisConsts& k) {
+    const float e0 = screen_e0(k);
+    return S < 1.5 * (double)e0 ? 0.75f * e0 : __builtin_inff();
+}
+
 __device__ __forceinline__ ScreenRow screen_row(double S, const LisConsts& k) {
     const int T = screen_top(k) + 1;
     ScreenRow st;
     st.Xs = (float)(S * ldexp(4.0 / 3.0 * (1.0 + 6.0 * 0x1p-24), -T));
-    st.tau = (float)(S * (2.0 / 3.0 * (1.0 + 0x1p-19)));
+    st.tau = screen_tau(S, k);
     st.c = __int_as_float(0x3F2AAAAB - (T << 23));       // 2/3 rounded up, scaled
-    const float e0 = (float)(k.qb * k.qb + k.qc);
-    st.tie = __ballot(fabsf(st.tau - e0) < e0 * 0x1p-18f);
     return st;
 }
 
@@ -591,8 +599,8 @@ __device__ __forceinline__ uint32_t screen_key(uint32_t eb, const ScreenRow& st)
 
 // An undecided key somewhere in the wavefront: chk is the largest residue
 // (shifted to the top 23 bits) over the lane's keys.
-__device__ __forceinline__ bool screen_failed(uint32_t chk, const ScreenRow& st) {
-    return (st.tie | __ballot(chk >= 0u - (kScreenZone << 9))) != 0;
+__device__ __forceinline__ bool screen_failed(uint32_t chk) {
+    return __ballot(chk >= 0u - (kScreenZone << 9)) != 0;
 }
 
 // Wavefronts per SIMD the register allocation aims for: the logits of NC chunks
@@ -687,6 +695,23 @@ __device__ __forceinline__ RowState screen_exact(double S, const LisConsts& k) {
     return st;
 }
 
+// The exact S 2^-n from the e bits of a tile (cold: kept behind its branch).
+template <int NC, int NT>
+__device__ __forceinline__ double screen_sum(const int (&lg)[NC][8]) {
+    double part[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+#pragma unroll
+        for (int t = 0; t < (c < NC - 1 ? 8 : NT); ++t) {
+            int eb = lg[c][t];
+            asm volatile("" : "+v"(eb));
+            part[t & 3] += (double)__int_as_float(eb);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return row4_sum((part[0] + part[1]) + (part[2] + part[3]));
+}
+
 // Screened form of tile_iexp: lg holds the e bits afterwards (0 for masked
 // keys of the last chunk).  EXACT: the row sum S is exact (every key added in
 // binary64, 5 cycles more a key); kernels that overwrite a chunk's e before the
@@ -720,25 +745,13 @@ __device__ __forceinline__ ScreenRow tile_iexp_screen(int (&lg)[NC][8], const Li
     }
     S = row4_sum((part[0] + part[1]) + (part[2] + part[3]));
     ScreenRow st = screen_row(S, k);
+    if (!EXACT) {
+        const double t = 1.5 * (double)screen_e0(k);
+        if (__builtin_expect(__ballot(fabs(S - t) < t * 0x1p-21) != 0, 0))
+            st.tau = screen_tau(screen_sum<NC, NT>(lg), k);
+    }
     st.mc = mc;
     return st;
-}
-
-// The exact S 2^-n from the e bits of a tile (cold: kept behind its branch).
-template <int NC, int NT>
-__device__ __forceinline__ double screen_sum(const int (&lg)[NC][8]) {
-    double part[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-#pragma unroll
-        for (int t = 0; t < (c < NC - 1 ? 8 : NT); ++t) {
-            int eb = lg[c][t];
-            asm volatile("" : "+v"(eb));
-            part[t & 3] += (double)__int_as_float(eb);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    return row4_sum((part[0] + part[1]) + (part[2] + part[3]));
 }
 
 // bf16 operand of P = 2^(top - code) of chunk c (top <= 15) from the screened
@@ -765,7 +778,7 @@ __device__ __forceinline__ u32x4 chunk_pbits_screen(const int (&lg)[NC][8], cons
         // the exponent fields (4 bits) of both, plus the bias
         pb[w] = (__builtin_amdgcn_perm(b1, b0, 0x07060302u) & 0x07800780u) + 0x3F803F80u;
     }
-    undecided = screen_failed(chk, st);
+    undecided = screen_failed(chk);
     return pb;
 }
 
@@ -801,17 +814,22 @@ __device__ __forceinline__ u32x4 chunk_pbits_diff(const int (&lg)[8], const Scre
 
 // The same, one key at a time through 512 dwords of LDS that belong to the
 // wavefront (its S 2^-n follows them), so that the cold code needs few
-// registers.
-__device__ __forceinline__ u32x4 chunk_pbits_exact_lds(const int (&e)[8], const LisConsts& k,
-                                                       uint32_t* scr, int lane) {
+// registers, and only for the keys of which a lane's is undecided (nearly always
+// one of the eight; a chunk cost 0.5 to 0.7 us with all eight, in a launch of few
+// tiles).
+__device__ __forceinline__ u32x4 chunk_pbits_exact_lds(const int (&e)[8], const ScreenRow& st,
+                                                       const LisConsts& k, uint32_t* scr, int lane) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) scr[64 * t + lane] = (uint32_t)e[t];
     const RowState ex = screen_exact(*reinterpret_cast<const double*>(scr + 512 + 2 * lane), k);
     const uint32_t kr = ((uint32_t)(k.top + 1) << 25) - 1u;
 #pragma unroll 1
     for (int t = 0; t < 8; ++t) {
-        const int eb = (int)scr[64 * t + lane] + (k.n << 23);
-        scr[64 * t + lane] = (127u + code_rev_f(eb, ex, kr)) << 7;
+        const uint32_t eb = scr[64 * t + lane];
+        const uint32_t b = screen_key(eb, st);
+        uint32_t x = b >> 23;
+        if (screen_failed(b << 9)) x = code_rev_f((int)eb + (k.n << 23), ex, kr);
+        scr[64 * t + lane] = (127u + x) << 7;
     }
     u32x4 pb;
 #pragma unroll
@@ -840,19 +858,23 @@ __device__ __forceinline__ void chunk_codes_screen(int (&code)[8], const int (&l
         const int cd = top - (int)(b >> 23);
         code[t] = (c == NC - 1 && e == 0u) ? 0 : cd;
     }
-    undecided = screen_failed(chk, st);
+    undecided = screen_failed(chk);
 }
 
 // The codes of an undecided chunk by the binary64 form, as chunk_pbits_exact_lds.
 __device__ __forceinline__ void chunk_codes_exact_lds(int (&code)[8], const int (&e)[8],
-                                                      const LisConsts& k, uint32_t* scr, int lane) {
+                                                      const ScreenRow& st, const LisConsts& k,
+                                                      uint32_t* scr, int lane) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) scr[64 * t + lane] = (uint32_t)e[t];
     const RowState ex = screen_exact(*reinterpret_cast<const double*>(scr + 512 + 2 * lane), k);
 #pragma unroll 1
     for (int t = 0; t < 8; ++t) {
-        const int eb = (int)scr[64 * t + lane];
-        scr[64 * t + lane] = eb != 0 ? (uint32_t)code_f(eb + (k.n << 23), ex, k.top) : 0u;
+        const uint32_t eb = scr[64 * t + lane];
+        const uint32_t b = screen_key(eb, st);
+        int cd = screen_top(k) - (int)(b >> 23);
+        if (screen_failed(b << 9)) cd = code_f((int)eb + (k.n << 23), ex, k.top);
+        scr[64 * t + lane] = eb != 0 ? (uint32_t)cd : 0u;
     }
 #pragma unroll
     for (int t = 0; t < 8; ++t) code[t] = (int)scr[64 * t + lane];
@@ -1266,7 +1288,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
         for (int c = 0; c < NC; ++c) {
             bool undecided;
             u32x4 pb = chunk_pbits_screen<NC, NT, true>(cur, st, c, undecided);
-            if (__builtin_expect(undecided, 0)) pb = chunk_pbits_exact_lds(cur[c], k, scr, lane);
+            if (__builtin_expect(undecided, 0)) pb = chunk_pbits_exact_lds(cur[c], st, k, scr, lane);
             if (HALF && c == NC - 1)
                 chunk_mfma<DTMAX, true>(acc, pb, vt, p.ld, c, r, kg);
             else
@@ -1291,7 +1313,7 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
     auto codes_of = [&](int c, int (&code)[8]) __attribute__((always_inline)) {
         bool undecided;
         chunk_codes_screen<NC, NT>(code, cur, st, k, c, undecided);
-        if (__builtin_expect(undecided, 0)) chunk_codes_exact_lds(code, cur[c], k, scr, lane);
+        if (__builtin_expect(undecided, 0)) chunk_codes_exact_lds(code, cur[c], st, k, scr, lane);
     };
     if constexpr (DTMAX == 1) {
         // Dense code rows: the tile's rows are one contiguous span of the codes
