@@ -812,29 +812,41 @@ __device__ __forceinline__ u32x4 chunk_pbits_diff(const int (&lg)[8], const Scre
     return u32x4{x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16)};
 }
 
-// The same, one key at a time through 512 dwords of LDS that belong to the
-// wavefront (its S 2^-n follows them), so that the cold code needs few
-// registers, and only for the keys of which a lane's is undecided (nearly always
-// one of the eight; a chunk cost 0.5 to 0.7 us with all eight, in a launch of few
-// tiles).
-__device__ __forceinline__ u32x4 chunk_pbits_exact_lds(const int (&e)[8], const ScreenRow& st,
-                                                       const LisConsts& k, uint32_t* scr, int lane) {
+// The keys of an undecided chunk (the first nt of each lane) that some lane
+// leaves undecided, bit t for key t (uniform).
+__device__ __forceinline__ uint32_t undecided_keys(const int (&e)[8], const ScreenRow& st, int nt) {
+    uint32_t keys = 0;
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+        if (t < nt) keys |= screen_failed(screen_key((uint32_t)e[t], st) << 9) ? 1u << t : 0u;
+    return keys;
+}
+
+// The screened operand of an undecided chunk with its undecided keys by the
+// binary64 form: nearly always one of a lane's eight, so one at a time (all eight
+// took 0.5 to 0.7 us a chunk in a launch of few tiles), from 512 dwords of LDS
+// that belong to the wavefront (its S 2^-n follows them), so that the cold code
+// needs few registers.
+__device__ __forceinline__ void chunk_pbits_fix(u32x4& pb, const int (&e)[8], const ScreenRow& st,
+                                                const LisConsts& k, int nt, uint32_t* scr, int lane) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) scr[64 * t + lane] = (uint32_t)e[t];
+    uint32_t keys = undecided_keys(e, st, nt);
     const RowState ex = screen_exact(*reinterpret_cast<const double*>(scr + 512 + 2 * lane), k);
     const uint32_t kr = ((uint32_t)(k.top + 1) << 25) - 1u;
 #pragma unroll 1
-    for (int t = 0; t < 8; ++t) {
-        const uint32_t eb = scr[64 * t + lane];
-        const uint32_t b = screen_key(eb, st);
-        uint32_t x = b >> 23;
-        if (screen_failed(b << 9)) x = code_rev_f((int)eb + (k.n << 23), ex, kr);
-        scr[64 * t + lane] = (127u + x) << 7;
+    for (; keys != 0; keys &= keys - 1) {
+        const int t = __builtin_ctz(keys);
+        const int eb = (int)scr[64 * t + lane];
+        const uint32_t x = (127u + code_rev_f(eb + (k.n << 23), ex, kr)) << 7;
+        const uint32_t keep = t & 1 ? 0xFFFFu : 0xFFFF0000u;
+        const uint32_t put = t & 1 ? x << 16 : x;
+        static_for<4>([&](auto wi) __attribute__((always_inline)) {
+            constexpr int w = decltype(wi)::value;
+            const uint32_t mixed = (pb[w] & keep) | put;
+            pb[w] = (t >> 1) == w ? mixed : pb[w];
+        });
     }
-    u32x4 pb;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) pb[w] = scr[128 * w + lane] | (scr[128 * w + 64 + lane] << 16);
-    return pb;
 }
 
 // Codes of chunk c from the screened values (masked keys of the last chunk, held
@@ -861,23 +873,23 @@ __device__ __forceinline__ void chunk_codes_screen(int (&code)[8], const int (&l
     undecided = screen_failed(chk);
 }
 
-// The codes of an undecided chunk by the binary64 form, as chunk_pbits_exact_lds.
-__device__ __forceinline__ void chunk_codes_exact_lds(int (&code)[8], const int (&e)[8],
-                                                      const ScreenRow& st, const LisConsts& k,
-                                                      uint32_t* scr, int lane) {
+// The same for the codes of an undecided chunk.
+__device__ __forceinline__ void chunk_codes_fix(int (&code)[8], const int (&e)[8], const ScreenRow& st,
+                                                const LisConsts& k, int nt, uint32_t* scr, int lane) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) scr[64 * t + lane] = (uint32_t)e[t];
+    uint32_t keys = undecided_keys(e, st, nt);
     const RowState ex = screen_exact(*reinterpret_cast<const double*>(scr + 512 + 2 * lane), k);
 #pragma unroll 1
-    for (int t = 0; t < 8; ++t) {
-        const uint32_t eb = scr[64 * t + lane];
-        const uint32_t b = screen_key(eb, st);
-        int cd = screen_top(k) - (int)(b >> 23);
-        if (screen_failed(b << 9)) cd = code_f((int)eb + (k.n << 23), ex, k.top);
-        scr[64 * t + lane] = eb != 0 ? (uint32_t)cd : 0u;
+    for (; keys != 0; keys &= keys - 1) {
+        const int t = __builtin_ctz(keys);
+        const int eb = (int)scr[64 * t + lane];
+        const int cd = eb != 0 ? code_f(eb + (k.n << 23), ex, k.top) : 0;
+        static_for<8>([&](auto ui) __attribute__((always_inline)) {
+            constexpr int u = decltype(ui)::value;
+            code[u] = t == u ? cd : code[u];
+        });
     }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) code[t] = (int)scr[64 * t + lane];
 }
 
 // Codes of chunk c; in the last chunk masked keys (held as 0) get code 0 and
@@ -1288,7 +1300,8 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
         for (int c = 0; c < NC; ++c) {
             bool undecided;
             u32x4 pb = chunk_pbits_screen<NC, NT, true>(cur, st, c, undecided);
-            if (__builtin_expect(undecided, 0)) pb = chunk_pbits_exact_lds(cur[c], st, k, scr, lane);
+            if (__builtin_expect(undecided, 0))
+                chunk_pbits_fix(pb, cur[c], st, k, c == NC - 1 ? NT : 8, scr, lane);
             if (HALF && c == NC - 1)
                 chunk_mfma<DTMAX, true>(acc, pb, vt, p.ld, c, r, kg);
             else
@@ -1313,7 +1326,8 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
     auto codes_of = [&](int c, int (&code)[8]) __attribute__((always_inline)) {
         bool undecided;
         chunk_codes_screen<NC, NT>(code, cur, st, k, c, undecided);
-        if (__builtin_expect(undecided, 0)) chunk_codes_exact_lds(code, cur[c], st, k, scr, lane);
+        if (__builtin_expect(undecided, 0))
+            chunk_codes_fix(code, cur[c], st, k, c == NC - 1 ? NT : 8, scr, lane);
     };
     if constexpr (DTMAX == 1) {
         // Dense code rows: the tile's rows are one contiguous span of the codes
@@ -1368,9 +1382,14 @@ __device__ __forceinline__ void unit_tile(int (&cur)[NC][8], int (&nxt)[NC][8], 
 // spilled at 80; on the Swin-S shapes five and six measured the same without
 // it), and four otherwise (128 registers); rows of more than 8 chunks hold more
 // logits than three wavefronts per SIMD leave registers for: two.  Codes only:
-// what the rows need by themselves (seven chunks: 94 registers).
-constexpr int unit_waves_per_simd(int NC, bool FUSED, int DTMAX, int WPU) {
+// what the rows need by themselves (seven chunks: 94 registers).  Some fused
+// instances with half last chunks take one or two registers more by themselves
+// than a further wavefront leaves them, and are held to it (129 registers at
+// three chunks: 1600 units of 65 x 65 17.4 us, 15.5 with 128).
+constexpr int unit_waves_per_simd(int NC, bool FUSED, int DTMAX, bool HALF, int WPU) {
     if (!FUSED) return NC <= 2 ? 6 : NC <= 10 ? 4 : NC <= 16 ? 3 : 2;
+    if (HALF && NC <= 2 && DTMAX <= 2) return 7;
+    if (HALF && WPU == 4 && NC == 3) return 4;
     return NC > 8 ? 2 : WPU == 4 ? 3 : NC <= 2 && DTMAX <= 2 ? 5 : 4;
 }
 
@@ -1378,7 +1397,7 @@ constexpr int unit_waves_per_simd(int NC, bool FUSED, int DTMAX, int WPU) {
 // WPU wavefronts per unit (4, or fewer for units of few tiles, so that each
 // wavefront walks several; V^T staged by those 64 WPU threads).
 template <int NC, bool FUSED, int DTMAX, bool HALF, int WPU = 4>
-__global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, WPU)) void lis_unit_kernel(
+__global__ __launch_bounds__(64 * WPU, unit_waves_per_simd(NC, FUSED, DTMAX, HALF, WPU)) void lis_unit_kernel(
     LisArgs a, LisLaunch p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint16_t* vt = reinterpret_cast<uint16_t*>(smem);
