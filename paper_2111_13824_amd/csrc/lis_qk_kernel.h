@@ -262,6 +262,7 @@ __device__ __forceinline__ void qk_fix_chunks(f32x4 (&acc)[DTMAX], uint32_t todo
 constexpr int qk_waves(int NC) { return NC <= 10 ? 4 : 8; }
 constexpr int qk_waves_per_simd(int NC, bool FP) {
     if (!FP && NC == 4) return 4;       // some forms take 131 to 134 registers by themselves
+    if (FP && NC == 2) return 6;        // 83 (1536 units of 64 x 64 9.8 us, 9.0 with 80)
     return NC <= 8 ? 3 : 2;
 }
 constexpr int kQkGroup = 3;     // chunks whose K reads and bias are in flight together
