@@ -120,12 +120,12 @@ inline int unit_split(int64_t G, int tiles, int waves, int nc, size_t lds) {
     if (fill > 1 || nc < 8 || nc > 9) return (int)even;
     // Rows of 225 to 288 keys, more units than half the slots: the SIMDs that
     // get a wavefront more than the others end last, so the load of one is its
-    // wavefronts, rounded up, times the tiles each walks and the staging (0.3 of
+    // wavefronts, rounded up, times the tiles each walks and the staging (0.4 of
     // a tile).  300 units of 288 x 288 38.6 us undivided and 33.5 divided, 520 of
-    // 257 x 257 with a bias 84 and 70; 768 of 257 x 257 56 and 73.
+    // 257 x 257 with a bias 84 and 70; 768 of 257 x 257 56 and 73, 400 37.4 and 40.7.
     auto cost = [&](int64_t split) {
         const int64_t load = (G * split * waves + kSimds - 1) / kSimds;
-        return (double)load * ((double)((tiles + waves * split - 1) / (waves * split)) + 0.3);
+        return (double)load * ((double)((tiles + waves * split - 1) / (waves * split)) + 0.4);
     };
     int64_t best = 1;
     for (int64_t t = std::min<int64_t>(8, most); t >= 1; --t)
